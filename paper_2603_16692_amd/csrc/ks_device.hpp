@@ -14,8 +14,13 @@
 //    constants use Shoup's method (w' = floor(w * 2^64 / q)), products of two
 //    variables Montgomery's REDC with R = 2^64. Forward butterflies keep
 //    Harvey's [0, 4q) range, inverse butterflies [0, 2q).
-// Between kernels, Q-limb data is stored as canonical uint64 residues and
-// P-limb data in the lazy integer ranges stated at each kernel.
+// At the boundary every limb is canonical uint64 residues. Between the two
+// passes of a transform (the workspace arrays t1, ext1 and t2, and the caller's
+// array between the passes of ks_ntt / ks_intt) Q-limb words are "raw": the bits
+// of the integer-valued double as the pass left it, within 6q, which saves the
+// canonical reduction at the store (8 instructions) and the conversion at the
+// load (2) of every word. P-limb words there are in the lazy integer ranges
+// stated at each kernel.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -122,18 +127,33 @@ __device__ __forceinline__ double u2d(uint64_t v) {
   return __longlong_as_double((long long)(v | 0x4330000000000000ull)) - 4503599627370496.0;
 }
 
-// Canonical residue of an integer-valued |x| < 2^53, as uint64.
-__device__ __forceinline__ uint64_t f_canon(double x, double q, double qinv) {
-  double r = f_red(x, q, qinv);
-  r = r < 0.0 ? r + q : r;
-  return (uint64_t)__double_as_longlong(r + 4503599627370496.0) & 0x000FFFFFFFFFFFFFull;
+// Canonical residue in [0, q) of an integer-valued |x| <= 1.9q, as a double.
+// (x + 1/2)/q stays at least 1/(2q) > 2^-51 away from every integer, and for a
+// magnitude below 2 its computed value is off by at most 2^-53 (the rounding of
+// the fma) + 1.9 * 2^-53 (that of qinv) < 2^-51, so the floor is exact.
+__device__ __forceinline__ double f_canon_d(double x, double q, double qinv) {
+  return __fma_rn(-__builtin_floor(__fma_rn(x, qinv, 0.5 * qinv)), q, x);
 }
 
-// Canonical residue in [0, q) as a double.
-__device__ __forceinline__ double f_canon_d(double x, double q, double qinv) {
-  const double r = f_red(x, q, qinv);
-  return r < 0.0 ? r + q : r;
+// The same for an integer-valued |x| < 2^53.
+__device__ __forceinline__ double f_canon_wide_d(double x, double q, double qinv) {
+  return f_canon_d(f_red(x, q, qinv), q, qinv);
 }
+
+// Exact conversion of an integer-valued double in [0, 2^52).
+__device__ __forceinline__ uint64_t d2u(double v) {
+  return (uint64_t)__double_as_longlong(v + 4503599627370496.0) & 0x000FFFFFFFFFFFFFull;
+}
+
+// Canonical residue as uint64, of |x| <= 1.9q and of |x| < 2^53.
+__device__ __forceinline__ uint64_t f_canon(double x, double q, double qinv) { return d2u(f_canon_d(x, q, qinv)); }
+__device__ __forceinline__ uint64_t f_canon_wide(double x, double q, double qinv) {
+  return d2u(f_canon_wide_d(x, q, qinv));
+}
+
+// Raw words of Q-limb intermediates.
+__device__ __forceinline__ double raw2d(uint64_t v) { return __longlong_as_double((long long)v); }
+__device__ __forceinline__ uint64_t d2raw(double v) { return (uint64_t)__double_as_longlong(v); }
 
 // ------------------------------------------------------ arithmetics
 
@@ -161,6 +181,7 @@ struct ArI {
   uint64_t q, two_q;
   const uint64_t* tw;
   // Forward (Cooley-Tukey): X, Y in [0, 4q) -> X + W*Y, X - W*Y in [0, 4q).
+  template <bool RED>
   __device__ __forceinline__ void fwd(T& X, T& Y, uint32_t idx) const {
     const Tw t = load_tw(tw, idx);
     const uint64_t x = X >= two_q ? X - two_q : X;
@@ -168,8 +189,8 @@ struct ArI {
     X = x + v;
     Y = x - v + two_q;
   }
-  __device__ __forceinline__ void fwd_lazy(T& X, T& Y, uint32_t idx) const { fwd(X, Y, idx); }
   // Inverse (Gentleman-Sande): X, Y in [0, 2q) -> X + Y, W*(X - Y) in [0, 2q).
+  template <bool RED>
   __device__ __forceinline__ void inv(T& X, T& Y, uint32_t idx) const {
     const Tw t = load_tw(tw, idx);
     uint64_t s = X + Y;
@@ -178,45 +199,52 @@ struct ArI {
     X = s;
     Y = mul_shoup(d, t.w, t.ws, q);
   }
+  __device__ static constexpr bool fwd_red(int, bool) { return true; }
+  __device__ static constexpr bool inv_red(int, int) { return true; }
 };
 
-// FP64 arithmetic of one Q limb; `tw` is its balanced twiddle table.
-// Invariant: every value entering a butterfly satisfies |x| <= 2.2q.
+// FP64 arithmetic of one Q limb; `tw` is its balanced twiddle table. Values stay
+// below 8q < 2^53 in magnitude, where sums are exact and products with a
+// balanced twiddle (|w| <= q/2) below 2^102.
 //
-// Bounds (q < 2^50, so 1.5 * 2^-52 * |a| * q/2 <= 0.1875 |a| for a product
-// with a balanced twiddle): a reducing forward stage maps inputs within B to
-// outputs within q + 0.1875 B (+1); a lazy one (X not reduced) to within
-// 1.1875 B + 0.5q. The transforms alternate them, starting with a reducing
-// stage in every group of stages (sub_fwd), which keeps every value within
-// 2.2q: from B <= 2.2q, reduce -> 1.42q, lazy -> 2.18q, reduce -> 1.41q.
-// Products stay below 1.1 q^2 < 2^100 and sums below 2^53.
+// Bounds in units of q: a product of |a| <= A and a balanced twiddle is within
+// 0.5 + 0.1875 A (1.5 * 2^-52 * q/2 < 0.1875). A forward stage that reduces X maps
+// inputs within B to outputs within 1 + 0.1875 B, a lazy one to 0.5 + 1.1875 B.
+// sub_fwd reduces in its first stage only: a group of K <= 4 stages then maps
+// B <= 8 to at most 2.51 + 0.27 B (K = 3) or 3.48 + 0.32 B (K = 4, less for K < 3), so
+// a block pass of a raw input within 6 stays within 5.4 (E = 16; 4.1 with E <= 8)
+// and leaves 5.2 (3.6). A column pass starts from reduced values (within 1) and
+// skips even that reduction: 1 -> 1.69 -> 2.51 -> 3.48 -> 4.63 -> 5.99 for up to
+// 5 stages. The transforms are bound by the instructions they issue: reducing in
+// every other stage (one more of 9 per butterfly at E = 8) with canonical words
+// between the passes ran 973 us at (4, 2^16, 32), batch 8, against 946 us, and
+// 1334 against 1279 us at (8, 2^17, 56), batch 2.
+// An inverse stage maps B to X + Y within 2B and W*(X - Y) within 0.5 + 0.375 B:
+// from B <= 2 one lazy stage gives 4, and a reducing one (sums up to 8) returns to 2.
 struct ArF {
   using T = double;
   double q, qinv;
   const double* tw;
-  // X <- red(X) (|X| <= q/2 + 1); V = W*Y with |V| <= q/2 + 0.1875|Y|.
+  // RED: X is first reduced to |X| <= q/2 + 2.
+  template <bool RED>
   __device__ __forceinline__ void fwd(T& X, T& Y, uint32_t idx) const {
     const double w = tw[idx];
-    const double x = f_red(X, q, qinv);
+    const double x = RED ? f_red(X, q, qinv) : X;
     const double v = f_mul(Y, w, q, qinv);
     X = x + v;
     Y = x - v;
   }
-  // The same without reducing X (3 instructions fewer).
-  __device__ __forceinline__ void fwd_lazy(T& X, T& Y, uint32_t idx) const {
-    const double w = tw[idx];
-    const double v = f_mul(Y, w, q, qinv);
-    const double x = X;
-    X = x + v;
-    Y = x - v;
-  }
-  // X + Y reduced (|.| <= q/2 + 1); W*(X - Y) with |X - Y| <= 4q: |.| <= q/2 + 0.75q.
+  // RED: the sum is reduced.
+  template <bool RED>
   __device__ __forceinline__ void inv(T& X, T& Y, uint32_t idx) const {
     const double w = tw[idx];
     const double s = X + Y, d = X - Y;
-    X = f_red(s, q, qinv);
+    X = RED ? f_red(s, q, qinv) : s;
     Y = f_mul(d, w, q, qinv);
   }
+  __device__ static constexpr bool fwd_red(int rho, bool red0) { return rho == 0 && red0; }
+  // stage rho of a group of k inverse stages (executed from rho = k - 1 down to 0)
+  __device__ static constexpr bool inv_red(int rho, int k) { return rho == 0 || ((k - 1 - rho) & 1); }
 };
 
 // One subproblem of 2^K elements in registers. Local stage rho pairs
@@ -224,13 +252,14 @@ struct ArF {
 // (base << rho) + g of the bit-reversed table, where `base` is the table
 // index of the subproblem at its first stage (the butterfly tree of the
 // transform numbers node u's children 2u and 2u+1).
-// Local stages alternate reducing (even rho) and lazy (odd rho) butterflies.
+// Which stages reduce their running sums is the arithmetic's choice (fwd_red,
+// inv_red); RED0 = false tells it that the inputs are already reduced.
 //
 // PS >= 0: the table is a block's staged copy (base = 2^PS + p) whose stages
 // PS.. are stored group-major, entry (p << rho) + g of stage PS + rho at
 // 2^(PS + rho) + (g << PS) + p, so that the lanes of a wave (consecutive p)
 // read consecutive words.
-template <int K, int PS = -1, class Ar>
+template <int K, int PS = -1, bool RED0 = true, class Ar>
 __device__ __forceinline__ void sub_fwd(const Ar& A, typename Ar::T* x, uint32_t base) {
 #pragma unroll
   for (int rho = 0; rho < K; ++rho) {
@@ -241,10 +270,10 @@ __device__ __forceinline__ void sub_fwd(const Ar& A, typename Ar::T* x, uint32_t
       const uint32_t g = (uint32_t)(j >> (K - rho));
       const uint32_t idx = PS < 0 ? (base << rho) + g
                                   : base + ((1u << (PS + rho)) - (1u << PS)) + (g << (PS < 0 ? 0 : PS));
-      if (rho & 1)
-        A.fwd_lazy(x[j], x[j + dist], idx);
+      if (Ar::fwd_red(rho, RED0))
+        A.template fwd<true>(x[j], x[j + dist], idx);
       else
-        A.fwd(x[j], x[j + dist], idx);
+        A.template fwd<false>(x[j], x[j + dist], idx);
     }
   }
 }
@@ -257,7 +286,11 @@ __device__ __forceinline__ void sub_inv(const Ar& A, typename Ar::T* x, uint32_t
 #pragma unroll
     for (int j = 0; j < (1 << K); ++j) {
       if (j & dist) continue;
-      A.inv(x[j], x[j + dist], (base << rho) + (uint32_t)(j >> (K - rho)));
+      const uint32_t idx = (base << rho) + (uint32_t)(j >> (K - rho));
+      if (Ar::inv_red(rho, K))
+        A.template inv<true>(x[j], x[j + dist], idx);
+      else
+        A.template inv<false>(x[j], x[j + dist], idx);
     }
   }
 }

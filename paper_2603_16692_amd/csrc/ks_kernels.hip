@@ -38,11 +38,6 @@ __device__ __forceinline__ ArI ari(const DevTables& tb, const LimbC& L, int limb
   return ArI{L.q, L.two_q, (inverse ? tb.twi : tb.twf) + (size_t)limb * N * 2};
 }
 
-// Canonical double in [0, q) -> uint64.
-__device__ __forceinline__ uint64_t d2u(double v) {
-  return (uint64_t)__double_as_longlong(v + 4503599627370496.0) & 0x000FFFFFFFFFFFFFull;
-}
-
 // XCD-aware placement of block-pass workgroups. MI355X dispatches workgroup
 // w to XCD w mod 8, and each XCD has its own 4 MB L2. A block-pass "tile" is
 // one (limb, block) pair; the batch items of a tile read the same twiddles
@@ -85,8 +80,9 @@ __device__ __forceinline__ void inv_opaque(const Ar& A, typename Ar::T* v, typen
 // ------------------------------------------------------- standalone passes
 
 // Column pass of ks_ntt / ks_intt on x [items][nlimbs][N] (limb r uses prime
-// first + r). Q limbs: canonical in and out. P limbs: forward [0, 4q) in and
-// out; inverse [0, 2q) in, canonical out. The inverse includes N^-1.
+// first + r). Q limbs: forward canonical in, raw out; inverse raw in, canonical
+// out. P limbs: forward [0, 4q) in and out; inverse [0, 2q) in, canonical out.
+// The inverse includes N^-1.
 template <int LOGR, bool INV>
 __global__ __launch_bounds__(TC) void k_cols(DevTables tb, uint64_t* x, int first, int nlimbs, int log_m) {
   constexpr int R = 1 << LOGR;
@@ -100,17 +96,20 @@ __global__ __launch_bounds__(TC) void k_cols(DevTables tb, uint64_t* x, int firs
   if (limb < tb.ell) {
     const ArF A = arf(tb, L, limb, INV);
     double v[R];
-#pragma unroll
-    for (int i = 0; i < R; ++i) v[i] = u2d(a[c + (size_t)i * M]);
     if (!INV) {
-      sub_fwd<LOGR>(A, v, 1u);
+#pragma unroll
+      for (int i = 0; i < R; ++i) v[i] = u2d(a[c + (size_t)i * M]);
+      sub_fwd<LOGR, -1, false>(A, v, 1u);
+#pragma unroll
+      for (int i = 0; i < R; ++i) a[c + (size_t)i * M] = d2raw(v[i]);
     } else {
+#pragma unroll
+      for (int i = 0; i < R; ++i) v[i] = raw2d(a[c + (size_t)i * M]);
       sub_inv<LOGR>(A, v, 1u);
 #pragma unroll
-      for (int i = 0; i < R; ++i) v[i] = f_mul(v[i], L.ninv_d, L.qd, L.qinv);
+      for (int i = 0; i < R; ++i)  // |v| <= 2q: the product is within 0.88q
+        a[c + (size_t)i * M] = f_canon(f_mul(v[i], L.ninv_d, L.qd, L.qinv), L.qd, L.qinv);
     }
-#pragma unroll
-    for (int i = 0; i < R; ++i) a[c + (size_t)i * M] = f_canon(v[i], L.qd, L.qinv);
   } else {
     const ArI A = ari(tb, L, limb, INV);
     uint64_t v[R];
@@ -130,12 +129,13 @@ __global__ __launch_bounds__(TC) void k_cols(DevTables tb, uint64_t* x, int firs
 
 // Block pass of ks_ntt / ks_intt (and of d at the start of ModUp): one block
 // of one limb (first + l) of one item per workgroup (placed by xcd_tile),
-// src -> dst (may alias).
-// Forward: Q canonical in; P [0, 4q) in; canonical out. Inverse: canonical in;
-// out Q canonical, P [0, 2q); times N^-1 (canonical) when `scale` is set.
+// src -> dst (may alias). `whole`: the pass is the whole transform (no column
+// pass), with canonical words at both ends and, in the inverse, times N^-1.
+// Otherwise forward: Q raw in, P [0, 4q) in, canonical out; inverse: canonical
+// in, out Q raw (within 2q), P [0, 2q).
 template <int LOGM, int LOGE, bool INV>
 __global__ __launch_bounds__((1 << (LOGM - LOGE)), LOGM >= 12 ? 4 : 1) void k_blocks(DevTables tb, const uint64_t* src, uint64_t* dst,
-                                                                 int first, int nlimbs, int items, int scale) {
+                                                                 int first, int nlimbs, int items, int whole) {
   using B = BlockNtt<LOGM, LOGE>;
   extern __shared__ uint64_t lds[];
   const size_t N = (size_t)1 << tb.log_n;
@@ -154,21 +154,28 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), LOGM >= 12 ? 4 : 1) void k_bl
     double* ld = reinterpret_cast<double*>(lds);
     double v[B::E];
     if (!INV) {
+      if (whole) {
 #pragma unroll
-      for (int i = 0; i < B::E; ++i) v[i] = u2d(s[B::fr_pos(tid, i)]);
+        for (int i = 0; i < B::E; ++i) v[i] = u2d(s[B::fr_pos(tid, i)]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < B::E; ++i) v[i] = raw2d(s[B::fr_pos(tid, i)]);
+      }
       B::fwd(A, v, ld, tid, B0);
 #pragma unroll
-      for (int i = 0; i < B::E; ++i) d[B::cl_pos(tid, i)] = f_canon(v[i], L.qd, L.qinv);
+      for (int i = 0; i < B::E; ++i) d[B::cl_pos(tid, i)] = f_canon_wide(v[i], L.qd, L.qinv);
     } else {
 #pragma unroll
       for (int i = 0; i < B::E; ++i) v[i] = u2d(s[B::cl_pos(tid, i)]);
       B::inv(A, v, ld, tid, B0);
-      if (scale) {
+      if (whole) {
 #pragma unroll
-        for (int i = 0; i < B::E; ++i) v[i] = f_mul(v[i], L.ninv_d, L.qd, L.qinv);
+        for (int i = 0; i < B::E; ++i)
+          d[B::fr_pos(tid, i)] = f_canon(f_mul(v[i], L.ninv_d, L.qd, L.qinv), L.qd, L.qinv);
+      } else {
+#pragma unroll
+        for (int i = 0; i < B::E; ++i) d[B::fr_pos(tid, i)] = d2raw(v[i]);
       }
-#pragma unroll
-      for (int i = 0; i < B::E; ++i) d[B::fr_pos(tid, i)] = f_canon(v[i], L.qd, L.qinv);
     }
   } else {
     const ArI A = ari(tb, L, limb, INV);
@@ -183,7 +190,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), LOGM >= 12 ? 4 : 1) void k_bl
 #pragma unroll
       for (int i = 0; i < B::E; ++i) v[i] = s[B::cl_pos(tid, i)];
       B::inv(A, v, lds, tid, B0);
-      if (scale) {
+      if (whole) {
 #pragma unroll
         for (int i = 0; i < B::E; ++i) v[i] = reduce2(mul_shoup(v[i], L.ninv, L.ninv_s, L.q), L.q);
       }
@@ -233,7 +240,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), LOGM >= 12 ? 4 : 1) void k_ev
   }
   B::inv(arf(tb, L, i, true), v, reinterpret_cast<double*>(lds), tid, (uint32_t)(R + blk));
 #pragma unroll
-  for (int e = 0; e < B::E; ++e) t1[off + B::fr_pos(tid, e)] = f_canon(v[e], L.qd, L.qinv);
+  for (int e = 0; e < B::E; ++e) t1[off + B::fr_pos(tid, e)] = d2raw(v[e]);
 }
 
 // The HMUL or HROT part of one output element pair of limb i, added to a
@@ -263,11 +270,11 @@ constexpr int CT = CW * TC;         // threads per column workgroup
 
 // Digit j = j0 + blockIdx.y of item blockIdx.z, columns blockIdx.x*64 + lane:
 // inverse column pass of the digit's limbs of t1 (the block-pass output of d,
-// canonical), times N^-1 [(D_j/q_i)^-1]_{q_i}, giving canonical y_i (in LDS,
+// raw), times N^-1 [(D_j/q_i)^-1]_{q_i}, giving canonical y_i (in LDS,
 // [alpha][R][64] doubles); then for every target limb t in [tgt0, tgt1)
 // outside D_j: z_t = sum_i y_i [D_j/q_i]_t, forward column pass, store into
 // ext1 [items][nslots][nl][N] at slot (slot_stride ? j : 0). Q targets are
-// stored canonical, P targets in [0, 4q).
+// stored raw, P targets in [0, 4q).
 template <int LOGR>
 __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_modup_cols(DevTables tb, const uint64_t* t1, uint64_t* ext1, int j0,
                                                    int nslots, int slot_stride, int tgt0, int tgt1, int log_m) {
@@ -290,7 +297,7 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_modup_cols(DevTables 
       const uint64_t* a = t1 + ((size_t)item * ell + i) * N;
       double v[R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[r] = u2d(a[c + (size_t)r * M]);
+      for (int r = 0; r < R; ++r) v[r] = raw2d(a[c + (size_t)r * M]);
       sub_inv<LOGR>(arf(tb, L, i, true), v, 1u);
       const double w = tb.up_pre_d[i];
 #pragma unroll
@@ -308,7 +315,7 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_modup_cols(DevTables 
     const LimbC L = tb.limb[t];
     uint64_t* o = e + (size_t)t * N;
     if (t < ell) {
-      // |y * c| <= 2^50 * 2^49: each product is within 0.875q; fold every 8
+      // |y * c| <= 2^50 * 2^49: each product is within 0.69q; fold every 8
       double z[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) z[r] = 0.0;
@@ -323,9 +330,9 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_modup_cols(DevTables 
       }
 #pragma unroll
       for (int r = 0; r < R; ++r) z[r] = f_red(z[r], L.qd, L.qinv);
-      sub_fwd<LOGR>(arf(tb, L, t, false), z, 1u);
+      sub_fwd<LOGR, -1, false>(arf(tb, L, t, false), z, 1u);
 #pragma unroll
-      for (int r = 0; r < R; ++r) o[c + (size_t)r * M] = f_canon(z[r], L.qd, L.qinv);
+      for (int r = 0; r < R; ++r) o[c + (size_t)r * M] = d2raw(z[r]);
     } else {
       uint64_t z[R];
 #pragma unroll
@@ -369,6 +376,14 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_modup_cols(DevTables 
 typedef int mx_v4i __attribute__((ext_vector_type(4)));
 typedef int mx_v16i __attribute__((ext_vector_type(16)));
 
+// mx_pack of a canonical Q residue held as a double (v < 2^50): bytes 0..5
+// balanced, byte 6 = the rest, in [0, 4]. The 128 of each byte is added together
+// with the 2^52 that moves the integer into the mantissa (exact: the sum stays
+// below 2^52 + 2^51), and one exclusive or removes both.
+__device__ __forceinline__ uint64_t mx_pack_q(double v) {
+  return (uint64_t)__double_as_longlong(v + (4503599627370496.0 + 141289400074368.0)) ^ 0x4330808080808080ull;
+}
+
 // Signed bytes of the balanced digits of v < 2^60 (byte 7 is below 18):
 // adding 128 to each of the seven low bytes makes them the unsigned bytes of
 // v + 0x0080...80; flipping their top bit subtracts the 128 again modulo 256.
@@ -393,9 +408,10 @@ __device__ __forceinline__ void mx_halves(const mx_v16i& acc, double& lo, double
   hi = __fma_rn((double)b1, 65536.0, (double)b0);
 }
 
-// lo + 2^32 hi mod q for a Q prime: |result| <= q/2 + 1.
+// lo + 2^32 hi mod q for a Q prime, |result| <= 0.6q: the product is within
+// q/2 + 0.1875 * 2^46.1, and |lo| < 2^46.1 < 0.07q.
 __device__ __forceinline__ double mx_fold_q(double lo, double hi, double q, double qinv, double r32) {
-  return f_red(lo + f_mul(hi, r32, q, qinv), q, qinv);
+  return lo + f_mul(hi, r32, q, qinv);
 }
 
 // lo + 2^32 hi mod p for a P prime, in [0, 4p): with u = x + 2^51 >= 0 read
@@ -413,7 +429,7 @@ __device__ __forceinline__ uint64_t mx_fold_p(double lo, double hi, const LimbC&
 // runs the nm MFMA steps of every row r over the packed digits yp
 // ([pairs][R][64] x 16 bytes) again, so that only one target's R values are
 // live: for each row the fold mod t, then the forward column pass and, if
-// `st`, the store of the R rows. Q groups store canonical residues, P groups
+// `st`, the store of the R rows. Q groups store raw words, P groups
 // values in [0, 4p). The raised digits (and ModDown's t2) outgrow the caches,
 // so the stores are non-temporal (measured: 5% off the ModUp column kernel).
 template <int LOGR, bool QG, int NM, int PASS>
@@ -446,10 +462,10 @@ __device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2*
     asm volatile("" : "+v"(z[r]), "+v"(yo));
   }
   if constexpr (QG) {
-    sub_fwd<LOGR>(ArF{q, qi, tb.twf_d + (size_t)t * N}, z, 1u);
+    sub_fwd<LOGR, -1, false>(ArF{q, qi, tb.twf_d + (size_t)t * N}, z, 1u);
     if (st) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) __builtin_nontemporal_store(f_canon(z[r], q, qi), o + cc + (size_t)r * M);
+      for (int r = 0; r < R; ++r) __builtin_nontemporal_store(d2raw(z[r]), o + cc + (size_t)r * M);
     }
   } else {
     sub_fwd<LOGR>(ArI{L.q, L.two_q, tb.twf + (size_t)t * N * 2}, z, 1u);
@@ -508,11 +524,11 @@ __global__ __launch_bounds__(CT, LOGR == 4 ? 4 : 1) void k_modup_cols_mx(DevTabl
       const uint64_t* a = t1 + ((size_t)item * ell + i) * N;
       double v[R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[r] = u2d(a[c + (size_t)r * M]);
+      for (int r = 0; r < R; ++r) v[r] = raw2d(a[c + (size_t)r * M]);
       sub_inv<LOGR>(arf(tb, L, i, true), v, 1u);
       const double w = tb.up_pre_d[i];
 #pragma unroll
-      for (int r = 0; r < R; ++r) y[r] = mx_pack(d2u(f_canon_d(f_mul(v[r], w, L.qd, L.qinv), L.qd, L.qinv)));
+      for (int r = 0; r < R; ++r) y[r] = mx_pack_q(f_canon_d(f_mul(v[r], w, L.qd, L.qinv), L.qd, L.qinv));
     } else {
 #pragma unroll
       for (int r = 0; r < R; ++r) y[r] = 0;
@@ -596,6 +612,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
   if constexpr (QPATH) {
     const ArF A = arf(tb, L, t, false);
     double* ld = reinterpret_cast<double*>(lds);
+    constexpr int FOLD = LOGE >= 4 ? 3 : 4;
     double s0[B::E], s1[B::E], v[B::E];
 #pragma unroll
     for (int i = 0; i < B::E; ++i) s0[i] = s1[i] = 0.0;
@@ -609,19 +626,20 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
         const int slot = slot_stride ? j : 0;
         const uint64_t* src = ext1 + (((size_t)item * nslots + slot) * nl + t) * N + boff;
 #pragma unroll
-        for (int i = 0; i < B::E; ++i) v[i] = u2d(src[B::fr_pos(tid, i)]);
+        for (int i = 0; i < B::E; ++i) v[i] = raw2d(src[B::fr_pos(tid, i)]);
         fwd_opaque<B>(A, v, ld, tid, B0);
       }
       const uint64_t* k0 = evk + key_row(tb, j, 0, t) * N + boff;
       const uint64_t* k1 = evk + key_row(tb, j, 1, t) * N + boff;
-      // |v| <= 2.2q, key < q: each product is within 1.33q; fold every 4 digits
+      // |v| <= 3.6q (5.2q for E = 16), key < q: each product is within 1.85q
+      // (2.45q), so the sums stay below 8q when folded every FOLD digits
 #pragma unroll
       for (int i = 0; i < B::E; ++i) {
         const int x = B::cl_pos(tid, i);
         s0[i] += f_mul(v[i], u2d(k0[x]), L.qd, L.qinv);
         s1[i] += f_mul(v[i], u2d(k1[x]), L.qd, L.qinv);
       }
-      if (((j - j0) & 3) == 3) {
+      if ((j - j0) % FOLD == FOLD - 1) {
 #pragma unroll
         for (int i = 0; i < B::E; ++i) {
           s0[i] = f_red(s0[i], L.qd, L.qinv);
@@ -704,7 +722,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
 // ([k][R][64] uint64). Then for Q limbs i in [tgt0, tgt1), split over the
 // waves: z_i = sum_m y_m [P/p_m]_{q_i}, computed in FP64 as
 // y_hi [2^30 P/p_m] + y_lo [P/p_m] with y_m = y_hi 2^30 + y_lo; forward column
-// pass; t2 [items][2][ell][N] canonical.
+// pass; t2 [items][2][ell][N] raw.
 template <int LOGR>
 __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_moddown_cols(DevTables tb, const uint64_t* accp, uint64_t* t2, int tgt0,
                                                      int tgt1, int log_m) {
@@ -755,10 +773,10 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_moddown_cols(DevTable
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) z[r] = f_red(z[r], L.qd, L.qinv);
-    sub_fwd<LOGR>(arf(tb, L, i, false), z, 1u);
+    sub_fwd<LOGR, -1, false>(arf(tb, L, i, false), z, 1u);
     uint64_t* o = t2 + (((size_t)item * 2 + comp) * ell + i) * N;
 #pragma unroll
-    for (int r = 0; r < R; ++r) o[c + (size_t)r * M] = f_canon(z[r], L.qd, L.qinv);
+    for (int r = 0; r < R; ++r) o[c + (size_t)r * M] = d2raw(z[r]);
   }
 }
 
@@ -768,7 +786,7 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_moddown_cols(DevTable
 // k_moddown_cols, canonical y packed into LDS ([pair][R][64] x 16 bytes,
 // zero past the k sources and for columns past M). Phase 2: wave w takes the
 // column half w % 2 and the groups of four Q limbs w/2, w/2 + 4, ... that
-// meet [tgt0, tgt1); output t2 canonical.
+// meet [tgt0, tgt1); output t2 raw.
 template <int LOGR, int NM>
 __global__ __launch_bounds__(CT, LOGR == 4 ? 4 : 1) void k_moddown_cols_mx(DevTables tb, const uint64_t* accp, uint64_t* t2, int tgt0,
                                                        int tgt1, int log_m) {
@@ -824,7 +842,7 @@ __global__ __launch_bounds__(CT, LOGR == 4 ? 4 : 1) void k_moddown_cols_mx(DevTa
 
 // One block b of one Q limb i in [tgt0, tgt0 + ntgt) of one (item, component)
 // pair ic = item*2 + c per workgroup (placed by xcd_tile):
-// forward block pass of t2 (canonical), then out = (acc_Q - v) * P^-1 (canonical).
+// forward block pass of t2 (raw), then out = (acc_Q - v) * P^-1 (canonical).
 template <int LOGM, int LOGE>
 __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_blocks(DevTables tb, const uint64_t* t2,
                                                                          const uint64_t* acc, uint64_t* out,
@@ -845,7 +863,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_blocks(DevTabl
   const uint64_t* src = t2 + ((size_t)ic * tb.ell + i) * N + boff;
   double v[B::E];
 #pragma unroll
-  for (int e = 0; e < B::E; ++e) v[e] = u2d(src[B::fr_pos(tid, e)]);
+  for (int e = 0; e < B::E; ++e) v[e] = raw2d(src[B::fr_pos(tid, e)]);
   B::fwd(arf(tb, L, i, false), v, reinterpret_cast<double*>(lds), tid, B0);
   const uint64_t* a = acc + ((size_t)ic * tb.nl + i) * N + boff;
   uint64_t* o = out + ((size_t)ic * tb.ell + i) * N + boff;
@@ -858,7 +876,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_blocks(DevTabl
 #pragma unroll
     for (int e = 0; e < B::E; ++e) {
       const int x = B::cl_pos(tid, e);
-      // |acc - v| <= 3.2q, |P^-1| <= q/2
+      // |acc - v| <= 6.2q, |P^-1| <= q/2: the product is within 1.67q
       double w = f_mul(u2d(a[x]) - v[e], pinv, L.qd, L.qinv);
       if constexpr (MODE == 2) {  // HROT: sigma_g(c0) in component 0
         if (comp == 0) w += u2d(ev.a[r0 + galois_src((uint32_t)(boff + x), ev.galois, tb.log_n) - boff]);
@@ -869,7 +887,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_blocks(DevTabl
         else
           w += f_mul(a0, u2d(ev.b[r1 + x]), L.qd, L.qinv) + f_mul(u2d(ev.a[r1 + x]), u2d(ev.b[r0 + x]), L.qd, L.qinv);
       }
-      o[x] = f_canon(w, L.qd, L.qinv);
+      o[x] = MODE == 0 ? f_canon(w, L.qd, L.qinv) : f_canon_wide(w, L.qd, L.qinv);
     }
   };
   if (!ev.a)
@@ -908,7 +926,7 @@ __device__ __forceinline__ void stage_twiddles(T* tw, const T* table, uint32_t B
 //   s_c = -NTT(t2_c) + sum_{j in [j0, j1)} ext_j * evk[j][c],
 //   ext_j = d (i in D_j) or the forward block pass of ext1 slot j,
 //   out_c = s_c * P^-1 (canonical).
-// t2 and ext1 canonical in, |values| <= 2.2q inside. Inputs and key blocks are
+// t2 and ext1 raw in, |values| <= 5.4q inside. Inputs and key blocks are
 // loaded before the transform that precedes their use, so that their latency
 // overlaps it.
 template <int LOGM, int LOGE>
@@ -948,14 +966,16 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
     } else {
       const uint64_t* src = ext1 + (((size_t)item * nslots + (slot_stride ? j : 0)) * nl + i) * N + boff;
 #pragma unroll
-      for (int e = 0; e < B::E; ++e) x[e] = u2d(src[B::fr_pos(tid, e)]);
+      for (int e = 0; e < B::E; ++e) x[e] = raw2d(src[B::fr_pos(tid, e)]);
     }
   };
+  // Sums: within q/2 after a fold, plus at most 1.85q a product (2.45q for E = 16)
+  constexpr int FOLD = LOGE >= 4 ? 3 : 4;
   double s0[B::E], s1[B::E], cur[B::E], nxt[B::E];
   {
     const uint64_t* src = t2 + (((size_t)item * 2 + 0) * ell + i) * N + boff;
 #pragma unroll
-    for (int e = 0; e < B::E; ++e) cur[e] = u2d(src[B::fr_pos(tid, e)]);
+    for (int e = 0; e < B::E; ++e) cur[e] = raw2d(src[B::fr_pos(tid, e)]);
   }
   if constexpr (TWL) {
     stage_twiddles<LOGM, B::LAST_S0>(tw, tb.twf_d + (size_t)i * N, (uint32_t)(R + b), tid, B::T);
@@ -964,18 +984,18 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
   {
     const uint64_t* src = t2 + (((size_t)item * 2 + 1) * ell + i) * N + boff;
 #pragma unroll
-    for (int e = 0; e < B::E; ++e) nxt[e] = u2d(src[B::fr_pos(tid, e)]);
+    for (int e = 0; e < B::E; ++e) nxt[e] = raw2d(src[B::fr_pos(tid, e)]);
   }
   fwd_opaque<B, TWL>(A, cur, ld, tid, B0);
 #pragma unroll
   for (int e = 0; e < B::E; ++e) {
-    s0[e] = -cur[e];
+    s0[e] = -f_red(cur[e], L.qd, L.qinv);
     cur[e] = nxt[e];
   }
   if (DEEP && j0 < j1) load_digit(j0, nxt);
   fwd_opaque<B, TWL>(A, cur, ld, tid, B0);
 #pragma unroll
-  for (int e = 0; e < B::E; ++e) s1[e] = -cur[e];
+  for (int e = 0; e < B::E; ++e) s1[e] = -f_red(cur[e], L.qd, L.qinv);
   for (int j = j0; j < j1; ++j) {
     if constexpr (DEEP) {
 #pragma unroll
@@ -1004,7 +1024,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
       s0[e] += f_mul(cur[e], w0[e], L.qd, L.qinv);
       s1[e] += f_mul(cur[e], w1[e], L.qd, L.qinv);
     }
-    if (((j - j0) & 3) == 3) {
+    if ((j - j0) % FOLD == FOLD - 1) {
 #pragma unroll
       for (int e = 0; e < B::E; ++e) {
         s0[e] = f_red(s0[e], L.qd, L.qinv);
@@ -1020,10 +1040,14 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
 #pragma unroll
     for (int e = 0; e < B::E; ++e) {
       const int x = B::cl_pos(tid, e);
-      double v0 = f_mul(f_red(s0[e], L.qd, L.qinv), pinv, L.qd, L.qinv);
-      double v1 = f_mul(f_red(s1[e], L.qd, L.qinv), pinv, L.qd, L.qinv);
-      if constexpr (MODE != 0)  // |v| stays below 3q
+      // |s| <= 6.1q, |P^-1| <= q/2: the products are within 1.65q
+      double v0 = f_mul(s0[e], pinv, L.qd, L.qinv);
+      double v1 = f_mul(s1[e], pinv, L.qd, L.qinv);
+      if constexpr (MODE != 0) {  // |v| stays below 4q
         add_eval<MODE == 2>(L, ev, r0 + x, r1 + x, (uint32_t)(boff + x), tb.log_n, v0, v1);
+        v0 = f_red(v0, L.qd, L.qinv);
+        v1 = f_red(v1, L.qd, L.qinv);
+      }
       __builtin_nontemporal_store(f_canon(v0, L.qd, L.qinv), out + r0 + x);  // the result is not read again here
       __builtin_nontemporal_store(f_canon(v1, L.qd, L.qinv), out + r1 + x);
     }
@@ -1112,12 +1136,12 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_pre(DevTables 
   {
     const uint64_t* src = t2 + (((size_t)item * 2 + c) * ell + i) * N + boff;
 #pragma unroll
-    for (int e = 0; e < B::E; ++e) v[e] = u2d(src[B::fr_pos(tid, e)]);
+    for (int e = 0; e < B::E; ++e) v[e] = raw2d(src[B::fr_pos(tid, e)]);
   }
   fwd_opaque<B>(arf(tb, L, i, false), v, reinterpret_cast<double*>(lds), tid, (uint32_t)R + b);
   double sum[B::E];
 #pragma unroll
-  for (int e = 0; e < B::E; ++e) sum[e] = -v[e];  // |v| <= 2.2q
+  for (int e = 0; e < B::E; ++e) sum[e] = -f_red(v[e], L.qd, L.qinv);
   for (int j = 0; j < tb.ndig; ++j) {
     const uint64_t* src = j == own ? d + ((size_t)item * ell + i) * N + boff
                                    : ext1 + (((size_t)item * tb.ndig + j) * nl + i) * N + boff;
@@ -1127,7 +1151,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_pre(DevTables 
       const int x = B::cl_pos(tid, e);
       sum[e] += f_mul(u2d(src[x]), u2d(key[x]), L.qd, L.qinv);  // canonical operands: within 0.875q
     }
-    if ((j & 3) == 3) {  // 2.2q + 4 * 0.875q stays below 8q <= 2^53
+    if ((j & 7) == 7) {  // q/2 + 8 * 0.875q stays below 8q < 2^53
 #pragma unroll
       for (int e = 0; e < B::E; ++e) sum[e] = f_red(sum[e], L.qd, L.qinv);
     }
@@ -1138,7 +1162,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_pre(DevTables 
 #pragma unroll
   for (int e = 0; e < B::E; ++e) {
     const int x = B::cl_pos(tid, e);
-    double o = f_mul(f_red(sum[e], L.qd, L.qinv), pinv, L.qd, L.qinv);
+    double o = f_mul(sum[e], pinv, L.qd, L.qinv);  // |sum| <= 6.7q: within 1.76q
     if (ev.a) {
       if (ev.galois) {  // HROT: sigma(c0) joins component 0
         if (c == 0) o += u2d(ev.a[r0 + x - (boff + x) + galois_src((uint32_t)(boff + x), ev.galois, tb.log_n)]);
@@ -1149,6 +1173,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_pre(DevTables 
         else
           o += f_mul(a0, u2d(ev.b[r1 + x]), L.qd, L.qinv) + f_mul(u2d(ev.a[r1 + x]), u2d(ev.b[r0 + x]), L.qd, L.qinv);
       }
+      o = f_red(o, L.qd, L.qinv);
     }
     __builtin_nontemporal_store(f_canon(o, L.qd, L.qinv), out + rc + x);
   }
@@ -1156,7 +1181,8 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_pre(DevTables 
 
 // ------------------------------------------------------ standalone kernels
 
-// ks_modup: forward block pass of every non-digit limb of ext (in place).
+// ks_modup: forward block pass of every non-digit limb of ext (in place; Q raw
+// in, P [0, 4q) in, canonical out).
 template <int LOGM, int LOGE>
 __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_ext_blocks(DevTables tb, uint64_t* ext) {
   using B = BlockNtt<LOGM, LOGE>;
@@ -1173,10 +1199,10 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_ext_blocks(DevTables t
   if (t < tb.ell) {
     double v[B::E];
 #pragma unroll
-    for (int e = 0; e < B::E; ++e) v[e] = u2d(a[B::fr_pos(tid, e)]);
+    for (int e = 0; e < B::E; ++e) v[e] = raw2d(a[B::fr_pos(tid, e)]);
     B::fwd(arf(tb, L, t, false), v, reinterpret_cast<double*>(lds), tid, B0);
 #pragma unroll
-    for (int e = 0; e < B::E; ++e) a[B::cl_pos(tid, e)] = f_canon(v[e], L.qd, L.qinv);
+    for (int e = 0; e < B::E; ++e) a[B::cl_pos(tid, e)] = f_canon_wide(v[e], L.qd, L.qinv);
   } else {
     uint64_t v[B::E];
 #pragma unroll
@@ -1445,22 +1471,22 @@ struct ColsInv {
 template <int LOGM, int LOGE>
 struct BlocksFwd {
   static hipError_t run(const DevTables& tb, const uint64_t* src, uint64_t* dst, int first, int nl, int items,
-                        int scale, hipStream_t s) {
+                        int whole, hipStream_t s) {
     using B = BlockNtt<LOGM, LOGE>;
     allow_lds<k_blocks<LOGM, LOGE, false>>();
     k_blocks<LOGM, LOGE, false><<<dim3(xcd_grid(nl << (tb.log_n - LOGM), items)), dim3(B::T),
-                                  block_lds<LOGM, LOGE>(), s>>>(tb, src, dst, first, nl, items, scale);
+                                  block_lds<LOGM, LOGE>(), s>>>(tb, src, dst, first, nl, items, whole);
     return hipGetLastError();
   }
 };
 template <int LOGM, int LOGE>
 struct BlocksInv {
   static hipError_t run(const DevTables& tb, const uint64_t* src, uint64_t* dst, int first, int nl, int items,
-                        int scale, hipStream_t s) {
+                        int whole, hipStream_t s) {
     using B = BlockNtt<LOGM, LOGE>;
     allow_lds<k_blocks<LOGM, LOGE, true>>();
     k_blocks<LOGM, LOGE, true><<<dim3(xcd_grid(nl << (tb.log_n - LOGM), items)), dim3(B::T),
-                                 block_lds<LOGM, LOGE>(), s>>>(tb, src, dst, first, nl, items, scale);
+                                 block_lds<LOGM, LOGE>(), s>>>(tb, src, dst, first, nl, items, whole);
     return hipGetLastError();
   }
 };
@@ -1656,7 +1682,7 @@ hipError_t launch_ntt(const DevTables& tb, int log_r, uint64_t* x, int first, in
   if (log_r > 0) e = by_logr<ColsFwd>(log_r, tb, x, first, nlimbs, items, log_m, s);
   if (e != hipSuccess) return e;
   return by_logm<BlocksFwd>(log_m, (long)(nlimbs << log_r) * items, tb, (const uint64_t*)x, x, first, nlimbs, items,
-                            0, s);
+                            log_r == 0 ? 1 : 0, s);
 }
 
 hipError_t launch_intt(const DevTables& tb, int log_r, uint64_t* x, int first, int nlimbs, int items, hipStream_t s) {
