@@ -10,10 +10,15 @@
 //    products of a value and a balanced twiddle (|w| <= q/2) stay below
 //    q^2 < 2^100. MI355X runs FP64 FMA at the full vector rate, which makes
 //    this about three times faster than 64-bit integer products.
-//  * ArI, for the P primes (p < 2^60): uint64 residues; products by fixed
-//    constants use Shoup's method (w' = floor(w * 2^64 / q)), products of two
-//    variables Montgomery's REDC with R = 2^64. Forward butterflies keep
-//    Harvey's [0, 4q) range, inverse butterflies [0, 2q).
+//  * ArI, for the P primes: uint64 residues, lazily reduced up to 2^64. The P
+//    primes are the largest p = 2^60 - delta = 1 (mod 2N), and delta < 2^29 for
+//    every N and count the library takes (the host checks it), so a value folds
+//    at bit 60 with one 32-bit multiply-add (p_red), and a product of two
+//    variables is a 128-bit product folded twice (p_mul). Products by fixed
+//    constants use Shoup's method (w' = floor(w * 2^64 / q)) with the low partial
+//    product of the quotient left out. A 32-bit multiply or multiply-add issues
+//    in 4.3 to 4.8 cycles per wavefront here, like any other vector instruction
+//    of this code, so what counts is the number of instructions.
 // At the boundary every limb is canonical uint64 residues. Between the two
 // passes of a transform (the workspace arrays t1, ext1 and t2, and the caller's
 // array between the passes of ks_ntt / ks_intt) Q-limb words are "raw": the bits
@@ -31,7 +36,8 @@ namespace ks {
 // Per-limb constants (one entry per prime of the extended basis).
 struct LimbC {
   uint64_t q;
-  uint64_t two_q;
+  uint64_t nq;         // 2^64 - q
+  uint64_t delta;      // 2^60 - q (P primes; below 2^29)
   uint64_t mont_ninv;  // -q^-1 mod 2^64
   uint64_t r2;         // 2^128 mod q
   uint64_t ninv, ninv_s;
@@ -39,10 +45,8 @@ struct LimbC {
   double qd;           // q as a double (exact for the Q primes)
   double qinv;         // fl(1 / q)
   double ninv_d;       // balanced N^-1 mod q (Q primes)
-  uint64_t r64, r64_s; // 2^64 mod q with its Shoup companion
   // Recombination of the int8-MFMA base conversion (see k_modup_cols_mx):
   double r32_d;        // balanced 2^32 mod q (Q primes)
-  uint64_t r32, r32_s; // 2^32 mod q with its Shoup companion (P primes)
   uint64_t cadj;       // (-2^51 - 2^83) mod q (P primes)
 };
 
@@ -90,11 +94,45 @@ __device__ __forceinline__ uint64_t mul_shoup(uint64_t a, uint64_t w, uint64_t w
   return a * w - hi * q;
 }
 
+// The same with the quotient's low partial product and carries left out (nq =
+// 2^64 - q): the quotient is at most 3 below Shoup's, which is at most 1 below
+// the true one, so the result is a*w mod q plus a multiple of q, in [0, 4q).
+// 13 multiplies and additions against 18.
+__device__ __forceinline__ uint64_t mul_shoup_lazy(uint64_t a, uint64_t w, uint64_t ws, uint64_t nq) {
+  const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
+  const uint32_t s0 = (uint32_t)ws, s1 = (uint32_t)(ws >> 32);
+  const uint64_t h = (uint64_t)a1 * s1 + __umulhi(a1, s0) + __umulhi(a0, s1);
+  return a * w + h * nq;
+}
+
 __device__ __forceinline__ uint64_t reduce2(uint64_t x, uint64_t q) { return x >= q ? x - q : x; }
 
-__device__ __forceinline__ uint64_t reduce4(uint64_t x, uint64_t q, uint64_t two_q) {
-  x = x >= two_q ? x - two_q : x;
-  return x >= q ? x - q : x;
+// ---- P primes p = 2^60 - delta: 2^60 = delta (mod p)
+
+constexpr uint64_t P_MASK = ((uint64_t)1 << 60) - 1;
+
+// Any x < 2^64 to below 2^60 + 2^33 (within p (1 + 2^-26)).
+__device__ __forceinline__ uint64_t p_red(uint64_t x, uint32_t delta) {
+  return (x & P_MASK) + (uint64_t)(uint32_t)(x >> 60) * delta;
+}
+// Any x < 2^64 to its canonical residue.
+__device__ __forceinline__ uint64_t p_canon(uint64_t x, uint64_t q, uint32_t delta) {
+  return reduce2(p_red(x, delta), q);
+}
+// a*b mod p for a, b < 2^60 + 2^33, below 1.5 * 2^60: the product's bits from 60
+// up times delta are below 2^89.1, and theirs below 2^58.6.
+__device__ __forceinline__ uint64_t p_mul(uint64_t a, uint64_t b, uint32_t delta) {
+  const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32), b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
+  const uint64_t lo = (uint64_t)a0 * b0;
+  uint64_t mid = (uint64_t)a0 * b1 + (lo >> 32);  // a1, b1 <= 2^28 + 2: no overflow
+  mid += (uint64_t)a1 * b0;
+  const uint64_t hi = (uint64_t)a1 * b1 + (mid >> 32);
+  const uint32_t h0 = __builtin_amdgcn_alignbit((uint32_t)hi, (uint32_t)mid, 28);
+  const uint32_t h1 = __builtin_amdgcn_alignbit((uint32_t)(hi >> 32), (uint32_t)hi, 28);
+  const uint64_t t = (((uint64_t)((uint32_t)mid & 0x0FFFFFFFu) << 32) | (uint32_t)lo) + (uint64_t)h0 * delta;
+  const uint64_t u = (uint64_t)h1 * delta + (t >> 32);
+  const uint64_t low = ((uint64_t)((uint32_t)u & 0x0FFFFFFFu) << 32) | (uint32_t)t;
+  return low + (uint64_t)(uint32_t)(u >> 28) * delta;
 }
 
 // Montgomery REDC of a*b for a*b < q * 2^64: returns a*b*2^-64 mod q in [0, 2q).
@@ -175,32 +213,40 @@ __device__ __forceinline__ Tw load_tw(const uint64_t* table, uint32_t idx) {
   return Tw{v.x, v.y};
 }
 
-// Integer arithmetic of one P limb; `tw` is its (w, Shoup) table.
+// Integer arithmetic of one P limb; `tw` is its (w, Shoup) table. Twiddle products
+// are in [0, 4q) for any 64-bit operand, so a forward stage adds 4q to the bound
+// of its inputs. sub_fwd reduces X (p_red, 3 instructions) in stages 0, 3, 6, ...
+// of a group: a group of any raw input (< 2^64) leaves at most 13q + 2^33, and a
+// column pass that starts from values below 2.2 * 2^60 skips the first reduction
+// (6.2, 10.2, 14.2, then reduced: 5, 9 for up to 5 stages).
+// An inverse stage maps inputs within 4q to a lazy sum within 8q and a product
+// in [0, 4q), and those to a reduced sum; exits are within 4q.
+// With conditional subtractions in every stage and the exact Shoup quotient a
+// butterfly was 27 instructions against 19, and a key product by Montgomery's
+// reduction 39 against 17 (p_mul): (4, 2^16, 32), batch 8, 946 us then and 863
+// now; (2, 2^13, 6), one ciphertext, 30.6 and 27.1.
 struct ArI {
   using T = uint64_t;
-  uint64_t q, two_q;
+  uint64_t q, nq;
+  uint32_t delta;
   const uint64_t* tw;
-  // Forward (Cooley-Tukey): X, Y in [0, 4q) -> X + W*Y, X - W*Y in [0, 4q).
   template <bool RED>
   __device__ __forceinline__ void fwd(T& X, T& Y, uint32_t idx) const {
     const Tw t = load_tw(tw, idx);
-    const uint64_t x = X >= two_q ? X - two_q : X;
-    const uint64_t v = mul_shoup(Y, t.w, t.ws, q);
+    const uint64_t x = RED ? p_red(X, delta) : X;
+    const uint64_t v = mul_shoup_lazy(Y, t.w, t.ws, nq);
     X = x + v;
-    Y = x - v + two_q;
+    Y = x + 4 * q - v;
   }
-  // Inverse (Gentleman-Sande): X, Y in [0, 2q) -> X + Y, W*(X - Y) in [0, 2q).
   template <bool RED>
   __device__ __forceinline__ void inv(T& X, T& Y, uint32_t idx) const {
     const Tw t = load_tw(tw, idx);
-    uint64_t s = X + Y;
-    s = s >= two_q ? s - two_q : s;
-    const uint64_t d = X - Y + two_q;
-    X = s;
-    Y = mul_shoup(d, t.w, t.ws, q);
+    const uint64_t s = X + Y, d = X + 8 * q - Y;
+    X = RED ? p_red(s, delta) : s;
+    Y = mul_shoup_lazy(d, t.w, t.ws, nq);
   }
-  __device__ static constexpr bool fwd_red(int, bool) { return true; }
-  __device__ static constexpr bool inv_red(int, int) { return true; }
+  __device__ static constexpr bool fwd_red(int rho, bool red0) { return rho % 3 == 0 && (rho > 0 || red0); }
+  __device__ static constexpr bool inv_red(int rho, int k) { return rho == 0 || ((k - 1 - rho) & 1); }
 };
 
 // FP64 arithmetic of one Q limb; `tw` is its balanced twiddle table. Values stay

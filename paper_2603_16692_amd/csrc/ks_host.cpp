@@ -161,6 +161,9 @@ bool derive_params(int dnum, int log_n, int ell, HostParams& hp) {
   const uint64_t step = 2 * (uint64_t)hp.n;
   if (!largest_primes(50, step, ell, hp.mod)) return false;
   if (!largest_primes(60, step, hp.k, hp.mod)) return false;
+  // the P-limb arithmetic folds at bit 60 with a factor below 2^29; holds for
+  // every N up to 2^17 and k up to 64 (the farthest is 2^60 - 364904447)
+  if (((uint64_t)1 << 60) - hp.mod.back() >= (uint64_t)1 << 29) return false;
   for (uint64_t q : hp.mod) hp.psi.push_back(smallest_root(q, hp.n));
   hp.key_ell = ell;
   return true;
@@ -235,19 +238,16 @@ void build_tables(const HostParams& hp, std::vector<uint64_t>& blob, DevTables& 
     const uint64_t q = hp.mod[t];
     LimbC L{};
     L.q = q;
-    L.two_q = 2 * q;
+    L.nq = ~q + 1;
+    L.delta = ((uint64_t)1 << 60) - q;
     L.mont_ninv = mont_neg_inv(q);
     const uint64_t r1 = (uint64_t)(((u128)1 << 64) % q);
     L.r2 = host_mulmod(r1, r1, q);
     L.ninv = inv_prime(n % q, q);
     L.ninv_s = shoup(L.ninv, q);
     L.red_s = shoup(1, q);
-    L.r64 = (uint64_t)(((u128)1 << 64) % q);
-    L.r64_s = shoup(L.r64, q);
-    L.r32 = ((uint64_t)1 << 32) % q;
-    L.r32_s = shoup(L.r32, q);
     {
-      uint64_t b = bal(L.r32, q);
+      uint64_t b = bal(((uint64_t)1 << 32) % q, q);
       std::memcpy(&L.r32_d, &b, sizeof(b));
     }
     // -(2^51 + 2^83) mod q

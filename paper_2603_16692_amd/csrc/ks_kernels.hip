@@ -35,7 +35,7 @@ __device__ __forceinline__ ArF arf(const DevTables& tb, const LimbC& L, int limb
 }
 __device__ __forceinline__ ArI ari(const DevTables& tb, const LimbC& L, int limb, bool inverse) {
   const size_t N = (size_t)1 << tb.log_n;
-  return ArI{L.q, L.two_q, (inverse ? tb.twi : tb.twf) + (size_t)limb * N * 2};
+  return ArI{L.q, L.nq, (uint32_t)L.delta, (inverse ? tb.twi : tb.twf) + (size_t)limb * N * 2};
 }
 
 // XCD-aware placement of block-pass workgroups. MI355X dispatches workgroup
@@ -81,8 +81,8 @@ __device__ __forceinline__ void inv_opaque(const Ar& A, typename Ar::T* v, typen
 
 // Column pass of ks_ntt / ks_intt on x [items][nlimbs][N] (limb r uses prime
 // first + r). Q limbs: forward canonical in, raw out; inverse raw in, canonical
-// out. P limbs: forward [0, 4q) in and out; inverse [0, 2q) in, canonical out.
-// The inverse includes N^-1.
+// out. P limbs: forward canonical in, below 2^64 out; inverse [0, 4q] in,
+// canonical out. The inverse includes N^-1.
 template <int LOGR, bool INV>
 __global__ __launch_bounds__(TC) void k_cols(DevTables tb, uint64_t* x, int first, int nlimbs, int log_m) {
   constexpr int R = 1 << LOGR;
@@ -116,11 +116,11 @@ __global__ __launch_bounds__(TC) void k_cols(DevTables tb, uint64_t* x, int firs
 #pragma unroll
     for (int i = 0; i < R; ++i) v[i] = a[c + (size_t)i * M];
     if (!INV) {
-      sub_fwd<LOGR>(A, v, 1u);
+      sub_fwd<LOGR, -1, false>(A, v, 1u);
     } else {
       sub_inv<LOGR>(A, v, 1u);
 #pragma unroll
-      for (int i = 0; i < R; ++i) v[i] = reduce2(mul_shoup(v[i], L.ninv, L.ninv_s, L.q), L.q);
+      for (int i = 0; i < R; ++i) v[i] = p_canon(mul_shoup_lazy(v[i], L.ninv, L.ninv_s, L.nq), L.q, L.delta);
     }
 #pragma unroll
     for (int i = 0; i < R; ++i) a[c + (size_t)i * M] = v[i];
@@ -131,8 +131,8 @@ __global__ __launch_bounds__(TC) void k_cols(DevTables tb, uint64_t* x, int firs
 // of one limb (first + l) of one item per workgroup (placed by xcd_tile),
 // src -> dst (may alias). `whole`: the pass is the whole transform (no column
 // pass), with canonical words at both ends and, in the inverse, times N^-1.
-// Otherwise forward: Q raw in, P [0, 4q) in, canonical out; inverse: canonical
-// in, out Q raw (within 2q), P [0, 2q).
+// Otherwise forward: Q raw in, P below 2^64 in, canonical out; inverse: canonical
+// in, out Q raw (within 2q), P [0, 4q].
 template <int LOGM, int LOGE, bool INV>
 __global__ __launch_bounds__((1 << (LOGM - LOGE)), LOGM >= 12 ? 4 : 1) void k_blocks(DevTables tb, const uint64_t* src, uint64_t* dst,
                                                                  int first, int nlimbs, int items, int whole) {
@@ -185,14 +185,15 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), LOGM >= 12 ? 4 : 1) void k_bl
       for (int i = 0; i < B::E; ++i) v[i] = s[B::fr_pos(tid, i)];
       B::fwd(A, v, lds, tid, B0);
 #pragma unroll
-      for (int i = 0; i < B::E; ++i) d[B::cl_pos(tid, i)] = reduce4(v[i], L.q, L.two_q);
+      for (int i = 0; i < B::E; ++i) d[B::cl_pos(tid, i)] = p_canon(v[i], L.q, L.delta);
     } else {
 #pragma unroll
       for (int i = 0; i < B::E; ++i) v[i] = s[B::cl_pos(tid, i)];
       B::inv(A, v, lds, tid, B0);
       if (whole) {
 #pragma unroll
-        for (int i = 0; i < B::E; ++i) v[i] = reduce2(mul_shoup(v[i], L.ninv, L.ninv_s, L.q), L.q);
+        for (int i = 0; i < B::E; ++i)
+          v[i] = p_canon(mul_shoup_lazy(v[i], L.ninv, L.ninv_s, L.nq), L.q, L.delta);
       }
 #pragma unroll
       for (int i = 0; i < B::E; ++i) d[B::fr_pos(tid, i)] = v[i];
@@ -274,7 +275,7 @@ constexpr int CT = CW * TC;         // threads per column workgroup
 // [alpha][R][64] doubles); then for every target limb t in [tgt0, tgt1)
 // outside D_j: z_t = sum_i y_i [D_j/q_i]_t, forward column pass, store into
 // ext1 [items][nslots][nl][N] at slot (slot_stride ? j : 0). Q targets are
-// stored raw, P targets in [0, 4q).
+// stored raw, P targets below 2^64.
 template <int LOGR>
 __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_modup_cols(DevTables tb, const uint64_t* t1, uint64_t* ext1, int j0,
                                                    int nslots, int slot_stride, int tgt0, int tgt1, int log_m) {
@@ -341,15 +342,15 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_modup_cols(DevTables 
         const size_t ci = 2 * ((size_t)(lo + s) * nl + t);
         const uint64_t w = ldc(tb.up_mat + ci), ws = ldc(tb.up_mat + ci + 1);
 #pragma unroll
-        for (int r = 0; r < R; ++r) z[r] += reduce2(mul_shoup(d2u(ys[(s * R + r) * TC + lane]), w, ws, L.q), L.q);
-        if ((s & 7) == 7) {  // keep the sum below 8q < 2^63
+        for (int r = 0; r < R; ++r) z[r] += mul_shoup_lazy(d2u(ys[(s * R + r) * TC + lane]), w, ws, L.nq);
+        if (s % 3 == 2) {  // keep the sum below 2^60 + 2^33 + 3 * 4q
 #pragma unroll
-          for (int r = 0; r < R; ++r) z[r] = reduce2(mul_shoup(z[r], 1, L.red_s, L.q), L.q);
+          for (int r = 0; r < R; ++r) z[r] = p_red(z[r], L.delta);
         }
       }
 #pragma unroll
-      for (int r = 0; r < R; ++r) z[r] = reduce2(mul_shoup(z[r], 1, L.red_s, L.q), L.q);
-      sub_fwd<LOGR>(ari(tb, L, t, false), z, 1u);
+      for (int r = 0; r < R; ++r) z[r] = p_red(z[r], L.delta);
+      sub_fwd<LOGR, -1, false>(ari(tb, L, t, false), z, 1u);
 #pragma unroll
       for (int r = 0; r < R; ++r) o[c + (size_t)r * M] = z[r];
     }
@@ -414,13 +415,15 @@ __device__ __forceinline__ double mx_fold_q(double lo, double hi, double q, doub
   return lo + f_mul(hi, r32, q, qinv);
 }
 
-// lo + 2^32 hi mod p for a P prime, in [0, 4p): with u = x + 2^51 >= 0 read
+// lo + 2^32 hi mod p for a P prime, below 2.1 * 2^60: with u = x + 2^51 >= 0 read
 // from the mantissa of x + 1.5 * 2^52, the value is
-// u_lo + 2^32 u_hi - 2^51 - 2^83, and cadj = (-2^51 - 2^83) mod p.
+// u_lo + 2^32 u_hi - 2^51 - 2^83, the bits of u_hi from 28 up fold at 2^60, and
+// cadj = (-2^51 - 2^83) mod p.
 __device__ __forceinline__ uint64_t mx_fold_p(double lo, double hi, const LimbC& L) {
   const uint64_t ul = (uint64_t)__double_as_longlong(lo + 6755399441055744.0) & 0x000FFFFFFFFFFFFFull;
   const uint64_t uh = (uint64_t)__double_as_longlong(hi + 6755399441055744.0) & 0x000FFFFFFFFFFFFFull;
-  return ul + mul_shoup(uh, L.r32, L.r32_s, L.q) + L.cadj;
+  return ul + ((uint64_t)((uint32_t)uh & 0x0FFFFFFFu) << 32) + (uint64_t)(uint32_t)(uh >> 28) * (uint32_t)L.delta +
+         L.cadj;
 }
 
 // Phase 2 of the MFMA column kernels for one target group. A lane in half h
@@ -430,7 +433,7 @@ __device__ __forceinline__ uint64_t mx_fold_p(double lo, double hi, const LimbC&
 // ([pairs][R][64] x 16 bytes) again, so that only one target's R values are
 // live: for each row the fold mod t, then the forward column pass and, if
 // `st`, the store of the R rows. Q groups store raw words, P groups
-// values in [0, 4p). The raised digits (and ModDown's t2) outgrow the caches,
+// values below 2^64. The raised digits (and ModDown's t2) outgrow the caches,
 // so the stores are non-temporal (measured: 5% off the ModUp column kernel).
 template <int LOGR, bool QG, int NM, int PASS>
 __device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2* yp, const ulonglong2 (&cst)[NM],
@@ -468,7 +471,7 @@ __device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2*
       for (int r = 0; r < R; ++r) __builtin_nontemporal_store(d2raw(z[r]), o + cc + (size_t)r * M);
     }
   } else {
-    sub_fwd<LOGR>(ArI{L.q, L.two_q, tb.twf + (size_t)t * N * 2}, z, 1u);
+    sub_fwd<LOGR, -1, false>(ari(tb, L, t, false), z, 1u);
     if (st) {
 #pragma unroll
       for (int r = 0; r < R; ++r) __builtin_nontemporal_store(z[r], o + cc + (size_t)r * M);
@@ -585,7 +588,7 @@ __global__ __launch_bounds__(CT, LOGR == 4 ? 4 : 1) void k_modup_cols_mx(DevTabl
 // digit j in [j0, j1): ext_j = (t in D_j) ? d : forward block pass of ext1;
 // s_c += ext_j * evk[j][c]. Then v_c = s_c (+ the previous acc if
 // `accumulate`), stored canonical. With `finalize` and t a P limb, the inverse
-// block pass of ModDown runs on v_c and leaves [0, 2q) in acc.
+// block pass of ModDown runs on v_c and leaves [0, 4q] in acc.
 // QPATH selects the Q-limb (FP64) or the P-limb (integer) body; the two are
 // separate kernels so that each gets its own register allocation.
 // With 8 elements per thread at M >= 2^12 the kernel fits 128 registers,
@@ -660,6 +663,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
     }
   } else {
   const ArI A = ari(tb, L, t, false);
+  const uint32_t delta = (uint32_t)L.delta;
   uint64_t s0[B::E], s1[B::E], v[B::E];
 #pragma unroll
   for (int i = 0; i < B::E; ++i) s0[i] = s1[i] = 0;
@@ -674,25 +678,30 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
 #pragma unroll
     for (int i = 0; i < B::E; ++i) {
       const int x = B::cl_pos(tid, i);
-      // running sums stay in [0, 2q): each Montgomery product is in [0, 2q)
-      s0[i] += mont_mul(v[i], k0[x], L.q, L.mont_ninv);
-      s0[i] = s0[i] >= L.two_q ? s0[i] - L.two_q : s0[i];
-      s1[i] += mont_mul(v[i], k1[x], L.q, L.mont_ninv);
-      s1[i] = s1[i] >= L.two_q ? s1[i] - L.two_q : s1[i];
+      // each product is below 1.5 * 2^60: folded every 8 digits, the sums stay below 2^64
+      const uint64_t vr = p_red(v[i], delta);
+      s0[i] += p_mul(vr, k0[x], delta);
+      s1[i] += p_mul(vr, k1[x], delta);
+    }
+    if (((j - j0) & 7) == 7) {
+#pragma unroll
+      for (int i = 0; i < B::E; ++i) {
+        s0[i] = p_red(s0[i], delta);
+        s1[i] = p_red(s1[i], delta);
+      }
     }
   }
 #pragma unroll
   for (int i = 0; i < B::E; ++i) {
-    // s < 2q, so s * r2 < 2 q^2 < q * 2^64
-    s0[i] = reduce2(mont_mul(s0[i], L.r2, L.q, L.mont_ninv), L.q);
-    s1[i] = reduce2(mont_mul(s1[i], L.r2, L.q, L.mont_ninv), L.q);
+    s0[i] = p_red(s0[i], delta);
+    s1[i] = p_red(s1[i], delta);
   }
   if (accumulate) {
 #pragma unroll
     for (int i = 0; i < B::E; ++i) {
       const int x = B::cl_pos(tid, i);
-      s0[i] = reduce2(s0[i] + a0[x], L.q);
-      s1[i] = reduce2(s1[i] + a1[x], L.q);
+      s0[i] += a0[x];
+      s1[i] += a1[x];
     }
   }
   if (finalize) {
@@ -707,8 +716,8 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
 #pragma unroll
     for (int i = 0; i < B::E; ++i) {
       const int x = B::cl_pos(tid, i);
-      a0[x] = s0[i];
-      a1[x] = s1[i];
+      a0[x] = p_canon(s0[i], L.q, delta);
+      a1[x] = p_canon(s1[i], L.q, delta);
     }
   }
   }
@@ -718,7 +727,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
 
 // Component blockIdx.y of item blockIdx.z, columns blockIdx.x*64 + lane:
 // inverse column pass of the k P limbs (accp [items][2][nl][N] at limbs ell..,
-// values in [0, 2q)), times N^-1 [(P/p_m)^-1]: canonical y_m < 2^60 in LDS
+// values in [0, 4q]), times N^-1 [(P/p_m)^-1]: canonical y_m < 2^60 in LDS
 // ([k][R][64] uint64). Then for Q limbs i in [tgt0, tgt1), split over the
 // waves: z_i = sum_m y_m [P/p_m]_{q_i}, computed in FP64 as
 // y_hi [2^30 P/p_m] + y_lo [P/p_m] with y_m = y_hi 2^30 + y_lo; forward column
@@ -745,7 +754,7 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_moddown_cols(DevTable
       sub_inv<LOGR>(ari(tb, L, ell + m, true), v, 1u);
       const uint64_t w = tb.dn_pre[2 * m], ws = tb.dn_pre[2 * m + 1];
 #pragma unroll
-      for (int r = 0; r < R; ++r) yl[(m * R + r) * TC + lane] = reduce2(mul_shoup(v[r], w, ws, L.q), L.q);
+      for (int r = 0; r < R; ++r) yl[(m * R + r) * TC + lane] = p_canon(mul_shoup_lazy(v[r], w, ws, L.nq), L.q, L.delta);
     }
   }
   __syncthreads();
@@ -811,7 +820,7 @@ __global__ __launch_bounds__(CT, LOGR == 4 ? 4 : 1) void k_moddown_cols_mx(DevTa
       sub_inv<LOGR>(ari(tb, L, ell + m, true), y, 1u);
       const uint64_t w = tb.dn_pre[2 * m], ws = tb.dn_pre[2 * m + 1];
 #pragma unroll
-      for (int r = 0; r < R; ++r) y[r] = mx_pack(reduce2(mul_shoup(y[r], w, ws, L.q), L.q));
+      for (int r = 0; r < R; ++r) y[r] = mx_pack(p_canon(mul_shoup_lazy(y[r], w, ws, L.nq), L.q, L.delta));
     } else {
 #pragma unroll
       for (int r = 0; r < R; ++r) y[r] = 0;
@@ -1069,9 +1078,9 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
 // twice the workgroups of K3 / K5 and a quarter to a third of their serial
 // chain, which is what a single small ciphertext needs.
 
-// P limbs: acc_c[t] = sum_j ext1[j][t] * evk[j][c][t] (Montgomery products,
-// running sums in [0, 2q)), then the inverse block pass; stored like K3's
-// finalize (accp in [0, 2q), first-round layout). Tile (P limb, block),
+// P limbs: acc_c[t] = sum_j ext1[j][t] * evk[j][c][t] (folded products below
+// 1.5 * 2^60), then the inverse block pass; stored like K3's
+// finalize (accp in [0, 4q], first-round layout). Tile (P limb, block),
 // item (item, component).
 template <int LOGM, int LOGE>
 __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_keymult_pre(DevTables tb, const uint64_t* ext1,
@@ -1088,6 +1097,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_keymult_pre(DevTables 
   const LimbC L = tb.limb[t];
   const int nl = tb.nl;
   const size_t boff = (size_t)b * B::M;
+  const uint32_t delta = (uint32_t)L.delta;
   uint64_t s[B::E];
 #pragma unroll
   for (int i = 0; i < B::E; ++i) s[i] = 0;
@@ -1097,12 +1107,15 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_keymult_pre(DevTables 
 #pragma unroll
     for (int i = 0; i < B::E; ++i) {
       const int x = B::cl_pos(tid, i);
-      s[i] += mont_mul(src[x], key[x], L.q, L.mont_ninv);
-      s[i] = s[i] >= L.two_q ? s[i] - L.two_q : s[i];
+      s[i] += p_mul(src[x], key[x], delta);
+    }
+    if ((j & 7) == 7) {
+#pragma unroll
+      for (int i = 0; i < B::E; ++i) s[i] = p_red(s[i], delta);
     }
   }
 #pragma unroll
-  for (int i = 0; i < B::E; ++i) s[i] = reduce2(mont_mul(s[i], L.r2, L.q, L.mont_ninv), L.q);
+  for (int i = 0; i < B::E; ++i) s[i] = p_red(s[i], delta);
   inv_opaque<B>(ari(tb, L, t, true), s, lds, tid, (uint32_t)R + b);
   uint64_t* a = acc + (((size_t)item * 2 + c) * nl + t) * N + boff;
 #pragma unroll
@@ -1182,7 +1195,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_pre(DevTables 
 // ------------------------------------------------------ standalone kernels
 
 // ks_modup: forward block pass of every non-digit limb of ext (in place; Q raw
-// in, P [0, 4q) in, canonical out).
+// in, P below 2^64 in, canonical out).
 template <int LOGM, int LOGE>
 __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_ext_blocks(DevTables tb, uint64_t* ext) {
   using B = BlockNtt<LOGM, LOGE>;
@@ -1209,7 +1222,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_ext_blocks(DevTables t
     for (int e = 0; e < B::E; ++e) v[e] = a[B::fr_pos(tid, e)];
     B::fwd(ari(tb, L, t, false), v, lds, tid, B0);
 #pragma unroll
-    for (int e = 0; e < B::E; ++e) a[B::cl_pos(tid, e)] = reduce4(v[e], L.q, L.two_q);
+    for (int e = 0; e < B::E; ++e) a[B::cl_pos(tid, e)] = p_canon(v[e], L.q, L.delta);
   }
 }
 
@@ -1320,13 +1333,13 @@ __global__ void k_keymult(DevTables tb, const uint64_t* ext, const uint64_t* evk
   for (int j = 0; j < tb.ndig; ++j) {
     s += mont_mul(ext[(((size_t)item * tb.ndig + j) * tb.nl + t) * N + x], evk[key_row(tb, j, c, t) * N + x],
                   L.q, L.mont_ninv);
-    s = s >= L.two_q ? s - L.two_q : s;
+    s = s >= 2 * L.q ? s - 2 * L.q : s;
   }
   acc[(((size_t)item * 2 + c) * tb.nl + t) * N + x] = reduce2(mont_mul(s, L.r2, L.q, L.mont_ninv), L.q);
 }
 
 // ks_moddown, first step: inverse block pass of the P limbs of acc
-// (canonical) into the work buffer accp (same layout), values in [0, 2q).
+// (canonical) into the work buffer accp (same layout), values in [0, 4q].
 template <int LOGM, int LOGE>
 __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_pblocks_inv(DevTables tb, const uint64_t* acc,
                                                                       uint64_t* accp) {

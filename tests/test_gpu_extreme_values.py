@@ -36,7 +36,8 @@ def _pattern(name, moduli, n):
 # every first-round size and elements-per-thread count of the block passes:
 # blocks of 2^8 to 2^14, remainders 1 to 4 of the stages over the rounds
 @pytest.mark.parametrize("dnum,log_n,ell,log_rs", [(3, 12, 7, (0, 1, 2, 4)), (2, 14, 5, (0, 1, 3, 5)),
-                                                   (5, 13, 10, (0, 3, 5)), (1, 9, 3, (0, 2))])
+                                                   (5, 13, 10, (0, 3, 5)), (1, 9, 3, (0, 2)),
+                                                   (11, 10, 11, (0, 2))])  # more digits than a sum holds unfolded
 @pytest.mark.parametrize("pattern", ["top", "ends", "one", "half"])
 def test_keyswitch_on_extreme_residues(dnum, log_n, ell, log_rs, pattern):
     import paper_2603_16692_amd as ks
