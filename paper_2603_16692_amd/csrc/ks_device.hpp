@@ -379,15 +379,18 @@ __device__ constexpr int pad_step(int d) { return d + (d >> 4); }
 //   x = hi * (M >> s0) + lo + j * L,  L = M >> (s0 + k),  p = tid + u*T,
 //   lo = p mod L, hi = p / L.
 // "FR" is the first round's layout (x = p + j*(M >> K1)); "CL" is the
-// coalesced layout x = tid + i*T. Forward transforms take FR and return CL;
-// inverse transforms take CL and return FR. Both layouts give consecutive
-// threads consecutive addresses for every register, so global loads and
-// stores at either end are coalesced; the last round's own layout
-// (x = tid*E + j) is transposed through LDS.
+// coalesced layout: wave w owns elements [64E w, 64E (w + 1)), its lane l holds
+// x = 64E w + 64 i + l in register i (x = tid + i*T for a block of at most 64
+// threads). Forward transforms take FR and return CL; inverse transforms take
+// CL and return FR. Both layouts give the lanes of a wave consecutive addresses
+// for every register, so global loads and stores at either end are coalesced;
+// the last round's own layout (x = tid*E + j) is transposed through LDS, and as
+// it holds the same elements in each wave as CL, without a workgroup barrier.
 template <int LOGM, int LOGE>
 struct BlockNtt {
   static constexpr int M = 1 << LOGM;
   static constexpr int E = 1 << LOGE;
+  static constexpr int LOGT = LOGM - LOGE;
   static constexpr int T = M / E;
   static constexpr int NR = (LOGM + LOGE - 1) / LOGE;
   static constexpr int K1 = LOGM - LOGE * (NR - 1);
@@ -411,8 +414,14 @@ struct BlockNtt {
     const int L = M >> (s0 + k);
     return (B0 << s0) + (uint32_t)(p / L);
   }
-  __device__ static __forceinline__ int fr_pos(int tid, int i) { return pos(0, tid, i >> K1, i & ((1 << K1) - 1)); }
-  __device__ static __forceinline__ int cl_pos(int tid, int i) { return tid + i * T; }
+  // Element of register i: a per-thread base plus a constant.
+  static constexpr int W = T < 64 ? T : 64;
+  __device__ static constexpr int fr_step(int i) { return (i >> K1) * T + (i & ((1 << K1) - 1)) * (M >> K1); }
+  __device__ static constexpr int cl_step(int i) { return i * W; }
+  __device__ static __forceinline__ int fr_base(int tid) { return tid; }
+  __device__ static __forceinline__ int cl_base(int tid) { return (tid / W) * (W * E) + (tid % W); }
+  __device__ static __forceinline__ int fr_pos(int tid, int i) { return fr_base(tid) + fr_step(i); }
+  __device__ static __forceinline__ int cl_pos(int tid, int i) { return cl_base(tid) + cl_step(i); }
 
   template <int K, int PS = -1, class Ar>
   __device__ static __forceinline__ void round_fwd(const Ar& A, typename Ar::T* x, int r, int tid, uint32_t B0) {
@@ -468,14 +477,14 @@ struct BlockNtt {
     }
   }
 
-  // Forward: x enters in FR, leaves in CL. B0 = R + b. Starts with a barrier
-  // so the LDS block may be reused right after a previous call. STAGED: the
+  // Forward: x enters in FR, leaves in CL. B0 = R + b. REUSE: a previous call
+  // read the LDS block, so a barrier precedes the first store. STAGED: the
   // twiddles are a staged copy (B0 = 1) with the last round's stages stored
   // group-major (sub_fwd with PS = LAST_S0).
-  template <bool STAGED = false, class Ar>
+  template <bool STAGED = false, bool REUSE = false, class Ar>
   __device__ static void fwd(const Ar& A, typename Ar::T* x, typename Ar::T* lds, int tid, uint32_t B0) {
     round_fwd<K1>(A, x, 0, tid, B0);
-    __syncthreads();
+    if (REUSE) __syncthreads();
     to_lds<K1>(x, lds, 0, tid);
 #pragma unroll
     for (int r = 1; r < NR; ++r) {
@@ -487,22 +496,22 @@ struct BlockNtt {
         round_fwd<LOGE>(A, x, r, tid, B0);
       to_lds<LOGE>(x, lds, r, tid);
     }
-    __syncthreads();
-    const typename Ar::T* c = lds + lds_pad(tid);  // CL: x = tid + i*T
+    exchange_sync(true);
+    const typename Ar::T* c = lds + lds_pad(cl_base(tid));
 #pragma unroll
-    for (int i = 0; i < E; ++i) x[i] = c[pad_step(i * T)];
+    for (int i = 0; i < E; ++i) x[i] = c[pad_step(cl_step(i))];
   }
 
-  // Inverse: x enters in CL, leaves in FR.
-  template <class Ar>
+  // Inverse: x enters in CL, leaves in FR. REUSE as in fwd.
+  template <bool REUSE = false, class Ar>
   __device__ static void inv(const Ar& A, typename Ar::T* x, typename Ar::T* lds, int tid, uint32_t B0) {
-    __syncthreads();
-    typename Ar::T* c = lds + lds_pad(tid);
+    if (REUSE) __syncthreads();
+    typename Ar::T* c = lds + lds_pad(cl_base(tid));
 #pragma unroll
-    for (int i = 0; i < E; ++i) c[pad_step(i * T)] = x[i];
+    for (int i = 0; i < E; ++i) c[pad_step(cl_step(i))] = x[i];
 #pragma unroll
     for (int r = NR - 1; r >= 1; --r) {
-      exchange_sync(r < NR - 1 && wave_local(r));  // the first read follows the CL stores
+      exchange_sync(r == NR - 1 || wave_local(r));  // the first read follows the CL stores
       from_lds<LOGE>(x, lds, r, tid);
       round_inv<LOGE>(A, x, r, tid, B0);
       to_lds<LOGE>(x, lds, r, tid);

@@ -62,19 +62,40 @@ inline unsigned xcd_grid(int ntiles, int items) { return (unsigned)(((ntiles + 7
 // runs several transforms would otherwise keep every LDS and twiddle address
 // of all rounds live from the first transform to the last, which costs more
 // registers than recomputing them.
-template <class B, bool STAGED = false, class Ar>
+template <class B, bool STAGED = false, bool REUSE = true, class Ar>
 __device__ __forceinline__ void fwd_opaque(const Ar& A, typename Ar::T* v, typename Ar::T* ld, int tid,
                                            uint32_t B0) {
   int t = tid;
   asm volatile("" : "+v"(t));
-  B::template fwd<STAGED>(A, v, ld, t, B0);
+  B::template fwd<STAGED, REUSE>(A, v, ld, t, B0);
 }
-template <class B, class Ar>
+template <class B, bool REUSE = true, class Ar>
 __device__ __forceinline__ void inv_opaque(const Ar& A, typename Ar::T* v, typename Ar::T* ld, int tid,
                                            uint32_t B0) {
   int t = tid;
   asm volatile("" : "+v"(t));
-  B::inv(A, v, ld, t, B0);
+  B::template inv<REUSE>(A, v, ld, t, B0);
+}
+
+// The E words of a thread of a block of M words at `src`, in the FR or CL
+// layout, as they are in memory: kernels that load ahead of use convert them
+// where they use them, since a conversion at the load would wait for it. Buffer
+// loads keep every address but one 32-bit offset in scalar registers, and that
+// offset is recomputed for each call (the hidden thread index) instead of being
+// held through the transforms.
+template <class B>
+__device__ __forceinline__ void load_words(const uint64_t* src, bool cl, int tid, uint64_t (&w)[B::E]) {
+  typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+  int t = tid;
+  asm volatile("" : "+v"(t));
+  const int base = 8 * (cl ? B::cl_base(t) : B::fr_base(t));
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t*>(src), 0, B::M * 8, 0x00027000);
+#pragma unroll
+  for (int i = 0; i < B::E; ++i) {
+    const v2u v = __builtin_amdgcn_raw_buffer_load_b64(rs, base, 8 * (cl ? B::cl_step(i) : B::fr_step(i)), 0);
+    w[i] = ((uint64_t)v.y << 32) | v.x;
+  }
 }
 
 // ------------------------------------------------------- standalone passes
@@ -244,20 +265,35 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), LOGM >= 12 ? 4 : 1) void k_ev
   for (int e = 0; e < B::E; ++e) t1[off + B::fr_pos(tid, e)] = d2raw(v[e]);
 }
 
-// The HMUL or HROT part of one output element pair of limb i, added to a
-// ModDown output (o0, o1) before its final reduction: (a0 b0, a0 b1 + a1 b0)
-// or (sigma_g(c0), 0). r0 / r1 index component 0 / 1 of the item's limb i,
-// slot t the element's slot in the limb.
-template <bool HROT>
-__device__ __forceinline__ void add_eval(const LimbC& L, const EvalIn& ev, size_t r0, size_t r1, uint32_t t,
-                                         int log_n, double& o0, double& o1) {
-  if constexpr (HROT) {
-    o0 += u2d(ev.a[r0 - t + galois_src(t, ev.galois, log_n)]);
+// The HMUL or HROT part of a thread's outputs of one block of limb i, added to
+// ModDown's (o0, o1) before their final reduction: (a0 b0, a0 b1 + a1 b0) or
+// (sigma_g(c0), 0). r0 / r1 are the words of component 0 / 1 where the item's
+// block of limb i starts, boff the block's first slot in the limb. All operand
+// words are loaded before the first use.
+template <class B>
+__device__ __forceinline__ void add_eval(const LimbC& L, EvalIn ev, size_t r0, size_t r1, uint32_t boff,
+                                         int tid, int log_n, double (&o0)[B::E], double (&o1)[B::E]) {
+  if (ev.galois) {
+    const uint64_t* c0 = ev.a + r0 - boff;
+    uint64_t w[B::E];
+#pragma unroll
+    for (int e = 0; e < B::E; ++e) w[e] = c0[galois_src(boff + (uint32_t)B::cl_pos(tid, e), ev.galois, log_n)];
+#pragma unroll
+    for (int e = 0; e < B::E; ++e) o0[e] += u2d(w[e]);
     return;
   }
-  const double a0 = u2d(ev.a[r0]), a1 = u2d(ev.a[r1]), b0 = u2d(ev.b[r0]), b1 = u2d(ev.b[r1]);
-  o0 += f_mul(a0, b0, L.qd, L.qinv);
-  o1 += f_mul(a0, b1, L.qd, L.qinv) + f_mul(a1, b0, L.qd, L.qinv);
+  uint64_t a0[B::E], a1[B::E], b0[B::E], b1[B::E];
+  load_words<B>(ev.a + r0, true, tid, a0);
+  load_words<B>(ev.b + r0, true, tid, b0);
+  load_words<B>(ev.b + r1, true, tid, b1);
+  load_words<B>(ev.a + r1, true, tid, a1);
+  // both branches end with o0: stores of different arrays at the end of the two
+  // would be merged into one through a selected address, which needs scratch memory
+#pragma unroll
+  for (int e = 0; e < B::E; ++e)
+    o1[e] += f_mul(u2d(a0[e]), u2d(b1[e]), L.qd, L.qinv) + f_mul(u2d(a1[e]), u2d(b0[e]), L.qd, L.qinv);
+#pragma unroll
+  for (int e = 0; e < B::E; ++e) o0[e] += f_mul(u2d(a0[e]), u2d(b0[e]), L.qd, L.qinv);
 }
 
 // ------------------------------------------------------------ ModUp (K2)
@@ -913,18 +949,35 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_blocks(DevTabl
 // of the forward pass) are stored group-major: group (p << (s - PS)) + g at
 // 2^s + (g << PS) + p. BlockNtt::fwd<true> with B0 = 1 and this table
 // computes what BlockNtt::fwd computes with B0 = R + b and the global table.
-template <int LOGM, int PS, class T>
-__device__ __forceinline__ void stage_twiddles(T* tw, const T* table, uint32_t B0, int tid, int nthreads) {
-  for (int x = tid; x < (1 << LOGM); x += nthreads) {
-    if (x == 0) continue;
-    const int s = 31 - __clz(x);
-    const uint32_t grp = (uint32_t)(x - (1 << s));
-    uint32_t pos = (uint32_t)x;
+// Thread tid moves entries tid + k T: past the first of them the stage is the
+// same for all threads. The loads and the stores are separate steps, so that all
+// loads of a thread are in flight together (one at a time, they were 5 us of
+// latency at the start of every workgroup).
+template <class B, class T>
+__device__ __forceinline__ void load_twiddles(T (&w)[B::E], const T* table, uint32_t B0, int tid) {
+  static_assert(B::E >= 2, "");
+  const int s0 = tid ? 31 - __clz(tid) : 0;
+  w[0] = table[(B0 << s0) + (uint32_t)(tid ? tid - (1 << s0) : 0)];  // entry 0 is not used
+#pragma unroll
+  for (int k = 1; k < B::E; ++k) {
+    const int s = B::LOGT + 31 - __builtin_clz(k);
+    w[k] = table[(B0 << s) + (uint32_t)(k * B::T - (1 << s)) + (uint32_t)tid];
+  }
+}
+template <class B, class T>
+__device__ __forceinline__ void store_twiddles(const T (&w)[B::E], T* tw, int tid) {
+  constexpr int PS = B::LAST_S0;
+#pragma unroll
+  for (int k = 0; k < B::E; ++k) {
+    const uint32_t x = (uint32_t)(tid + k * B::T);
+    const int s = k ? B::LOGT + 31 - __builtin_clz(k) : (tid ? 31 - __clz(tid) : 0);
+    uint32_t pos = x;
     if (s >= PS) {  // grp = (p << rho) + g
       const int rho = s - PS;
+      const uint32_t grp = x - (1u << s);
       pos = (1u << s) + ((grp & ((1u << rho) - 1)) << PS) + (grp >> rho);
     }
-    tw[pos] = table[(B0 << s) + grp];
+    tw[x ? pos : 0] = w[k];
   }
 }
 
@@ -937,9 +990,15 @@ __device__ __forceinline__ void stage_twiddles(T* tw, const T* table, uint32_t B
 //   out_c = s_c * P^-1 (canonical).
 // t2 and ext1 raw in, |values| <= 5.4q inside. Inputs and key blocks are
 // loaded before the transform that precedes their use, so that their latency
-// overlaps it.
+// overlaps it. That holds only while nothing waits for them early: words are kept
+// as loaded and converted at their use (a conversion or a register spill after the
+// loads waited for all of them), and 128 registers must hold the sums, the
+// current block, the next one and both key blocks (buffer loads, whose addresses
+// are scalar). With the waits where they belong, the twiddles staged with all loads
+// in flight and 6 barriers instead of 10, (4, 2^16, 32), batch 8, went from 863 to
+// 803 us and level 13 of it, batch 3, from 211 to 194.
 template <int LOGM, int LOGE>
-__global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4 : 1) void k_moddown_km_blocks(
+__global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM <= 12) ? 4 : 1) void k_moddown_km_blocks(
     DevTables tb, const uint64_t* d, const uint64_t* ext1, const uint64_t* evk, const uint64_t* t2, uint64_t* out,
     int j0, int j1, int nslots, int slot_stride, int tgt0, int ntgt, int items, EvalIn ev) {
   using B = BlockNtt<LOGM, LOGE>;
@@ -962,76 +1021,70 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
   const ArF A{L.qd, L.qinv, TWL ? tw : tb.twf_d + (size_t)i * N};
   const uint32_t B0 = TWL ? 1u : (uint32_t)(R + b);
   const int own = i / tb.alpha;  // the digit whose limbs include i: its input is d, already in NTT form
-  // Loads ahead of use: always the second t2 component and the first key
-  // component of a digit; with DEEP also the next digit's input and the
-  // second key component (registers allow it up to blocks of 2^12).
+  // Loads ahead of use (words as they are in memory, converted where they are
+  // used): always the second t2 component and the first key component of a
+  // digit; with DEEP also the next digit's input and the second key component
+  // (registers allow it up to blocks of 2^12).
   constexpr bool DEEP = LOGM <= 12;
   // input of digit j: d (CL layout) for the own digit, else ext1 (FR layout)
-  auto load_digit = [&](int j, double* x) {
-    if (j == own) {
-      const uint64_t* src = d + ((size_t)item * ell + i) * N + boff;
-#pragma unroll
-      for (int e = 0; e < B::E; ++e) x[e] = u2d(src[B::cl_pos(tid, e)]);
-    } else {
-      const uint64_t* src = ext1 + (((size_t)item * nslots + (slot_stride ? j : 0)) * nl + i) * N + boff;
-#pragma unroll
-      for (int e = 0; e < B::E; ++e) x[e] = raw2d(src[B::fr_pos(tid, e)]);
-    }
+  auto load_digit = [&](int j, uint64_t (&w)[B::E]) {
+    const uint64_t* src = j == own ? d + ((size_t)item * ell + i) * N + boff
+                                   : ext1 + (((size_t)item * nslots + (slot_stride ? j : 0)) * nl + i) * N + boff;
+    load_words<B>(src, j == own, tid, w);
   };
   // Sums: within q/2 after a fold, plus at most 1.85q a product (2.45q for E = 16)
   constexpr int FOLD = LOGE >= 4 ? 3 : 4;
-  double s0[B::E], s1[B::E], cur[B::E], nxt[B::E];
-  {
-    const uint64_t* src = t2 + (((size_t)item * 2 + 0) * ell + i) * N + boff;
+  const double pinv = ldc(tb.dn_pinv_d + i);
+  double s0[B::E], s1[B::E], cur[B::E];
+  uint64_t nxt[B::E];
+  load_words<B>(t2 + (((size_t)item * 2 + 0) * ell + i) * N + boff, false, tid, nxt);
+  double twr[B::E];
+  if constexpr (TWL) load_twiddles<B>(twr, tb.twf_d + (size_t)i * N, (uint32_t)(R + b), tid);
 #pragma unroll
-    for (int e = 0; e < B::E; ++e) cur[e] = raw2d(src[B::fr_pos(tid, e)]);
-  }
+  for (int e = 0; e < B::E; ++e) cur[e] = raw2d(nxt[e]);
+  load_words<B>(t2 + (((size_t)item * 2 + 1) * ell + i) * N + boff, false, tid, nxt);
   if constexpr (TWL) {
-    stage_twiddles<LOGM, B::LAST_S0>(tw, tb.twf_d + (size_t)i * N, (uint32_t)(R + b), tid, B::T);
+    store_twiddles<B>(twr, tw, tid);
     __syncthreads();
   }
-  {
-    const uint64_t* src = t2 + (((size_t)item * 2 + 1) * ell + i) * N + boff;
-#pragma unroll
-    for (int e = 0; e < B::E; ++e) nxt[e] = raw2d(src[B::fr_pos(tid, e)]);
-  }
-  fwd_opaque<B, TWL>(A, cur, ld, tid, B0);
+  fwd_opaque<B, TWL, false>(A, cur, ld, tid, B0);
 #pragma unroll
   for (int e = 0; e < B::E; ++e) {
     s0[e] = -f_red(cur[e], L.qd, L.qinv);
-    cur[e] = nxt[e];
+    cur[e] = raw2d(nxt[e]);
   }
   if (DEEP && j0 < j1) load_digit(j0, nxt);
   fwd_opaque<B, TWL>(A, cur, ld, tid, B0);
 #pragma unroll
   for (int e = 0; e < B::E; ++e) s1[e] = -f_red(cur[e], L.qd, L.qinv);
   for (int j = j0; j < j1; ++j) {
-    if constexpr (DEEP) {
-#pragma unroll
-      for (int e = 0; e < B::E; ++e) cur[e] = nxt[e];
-    }
     const uint64_t* k0 = evk + key_row(tb, j, 0, i) * N + boff;
     const uint64_t* k1 = evk + key_row(tb, j, 1, i) * N + boff;
-    double w0[B::E], w1[B::E];
-#pragma unroll
-    for (int e = 0; e < B::E; ++e) {
-      w0[e] = u2d(k0[B::cl_pos(tid, e)]);
-      if constexpr (DEEP) w1[e] = u2d(k1[B::cl_pos(tid, e)]);
-    }
+    uint64_t in[B::E], w0[B::E], w1[B::E];
     if constexpr (DEEP) {
+#pragma unroll
+      for (int e = 0; e < B::E; ++e) in[e] = nxt[e];
+    }
+    load_words<B>(k0, true, tid, w0);
+    if constexpr (DEEP) {
+      load_words<B>(k1, true, tid, w1);
       if (j + 1 < j1) load_digit(j + 1, nxt);
     } else {
-      load_digit(j, cur);
+      load_digit(j, in);
     }
-    if (j != own) fwd_opaque<B, TWL>(A, cur, ld, tid, B0);
-    if constexpr (!DEEP) {
+    if (j == own) {
 #pragma unroll
-      for (int e = 0; e < B::E; ++e) w1[e] = u2d(k1[B::cl_pos(tid, e)]);
+      for (int e = 0; e < B::E; ++e) cur[e] = u2d(in[e]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < B::E; ++e) cur[e] = raw2d(in[e]);
+      fwd_opaque<B, TWL>(A, cur, ld, tid, B0);
     }
+    if constexpr (!DEEP) load_words<B>(k1, true, tid, w1);
 #pragma unroll
     for (int e = 0; e < B::E; ++e) {
-      s0[e] += f_mul(cur[e], w0[e], L.qd, L.qinv);
-      s1[e] += f_mul(cur[e], w1[e], L.qd, L.qinv);
+      s0[e] += f_mul(cur[e], u2d(w0[e]), L.qd, L.qinv);
+      s1[e] += f_mul(cur[e], u2d(w1[e]), L.qd, L.qinv);
     }
     if ((j - j0) % FOLD == FOLD - 1) {
 #pragma unroll
@@ -1041,32 +1094,27 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
       }
     }
   }
-  const double pinv = tb.dn_pinv_d[i];
   const size_t r0 = (((size_t)item * 2 + 0) * ell + i) * N + boff, r1 = (((size_t)item * 2 + 1) * ell + i) * N + boff;
-  // MODE 0: plain KeySwitch, 1: HMUL, 2: HROT (chosen once per workgroup)
-  auto finish = [&](auto mode) {
-    constexpr int MODE = decltype(mode)::value;
+  // |s| <= 6.1q, |P^-1| <= q/2: the products are within 1.65q
+#pragma unroll
+  for (int e = 0; e < B::E; ++e) {
+    s0[e] = f_mul(s0[e], pinv, L.qd, L.qinv);
+    s1[e] = f_mul(s1[e], pinv, L.qd, L.qinv);
+  }
+  if (ev.a) {  // HMUL or HROT (chosen once per workgroup); |s| stays below 4q
+    add_eval<B>(L, ev, r0, r1, (uint32_t)boff, tid, tb.log_n, s0, s1);
 #pragma unroll
     for (int e = 0; e < B::E; ++e) {
-      const int x = B::cl_pos(tid, e);
-      // |s| <= 6.1q, |P^-1| <= q/2: the products are within 1.65q
-      double v0 = f_mul(s0[e], pinv, L.qd, L.qinv);
-      double v1 = f_mul(s1[e], pinv, L.qd, L.qinv);
-      if constexpr (MODE != 0) {  // |v| stays below 4q
-        add_eval<MODE == 2>(L, ev, r0 + x, r1 + x, (uint32_t)(boff + x), tb.log_n, v0, v1);
-        v0 = f_red(v0, L.qd, L.qinv);
-        v1 = f_red(v1, L.qd, L.qinv);
-      }
-      __builtin_nontemporal_store(f_canon(v0, L.qd, L.qinv), out + r0 + x);  // the result is not read again here
-      __builtin_nontemporal_store(f_canon(v1, L.qd, L.qinv), out + r1 + x);
+      s0[e] = f_red(s0[e], L.qd, L.qinv);
+      s1[e] = f_red(s1[e], L.qd, L.qinv);
     }
-  };
-  if (!ev.a)
-    finish(std::integral_constant<int, 0>{});
-  else if (!ev.galois)
-    finish(std::integral_constant<int, 1>{});
-  else
-    finish(std::integral_constant<int, 2>{});
+  }
+#pragma unroll
+  for (int e = 0; e < B::E; ++e) {
+    const uint32_t x = (uint32_t)B::cl_pos(tid, e);
+    __builtin_nontemporal_store(f_canon(s0[e], L.qd, L.qinv), out + r0 + x);  // the result is not read again here
+    __builtin_nontemporal_store(f_canon(s1[e], L.qd, L.qinv), out + r1 + x);
+  }
 }
 
 // --------------------------------- hoisted forward passes (KS_PLAN_HOIST_FWD)
