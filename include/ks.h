@@ -98,8 +98,10 @@ typedef struct {
    the KeySwitch subsection of the Background section, D_j -> PQ \ D_j and
    P -> Q) as an exact int8 matrix product on the matrix cores: residues and constants are split
    into balanced signed bytes, the int32 partial sums of each byte weight are
-   folded back modulo the target prime. The output is identical to the
-   default (FP64 / 64-bit integer) BConv. Supported when every digit and P
+   folded back modulo the target prime. The output is identical to that of the
+   FP64 / 64-bit integer BConv. A plan without the flag runs whichever form is
+   the faster one for the number of sources (the matrix form from 4 on, where it
+   is built). Supported when every digit and P
    have at most 16 primes, log_r <= 5 and the packed digits of a workgroup,
    ceil(max(alpha, k) / 4) * 2^log_r * 2 KB, fit in the 160 KB of LDS
    (ks_keyswitch returns KS_EUNSUP otherwise). */

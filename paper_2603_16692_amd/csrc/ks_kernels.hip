@@ -403,7 +403,7 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_modup_cols(DevTables 
 //   sum_s y_s c_{s,t} = sum_b 256^b C_b  (mod t),  C_b = sum_{s,a} d_{s,a} e_{s,a,t,b},
 // and every C_b is one entry of an int8 x int8 -> int32 matrix product with
 // K = 8 * (number of sources): rows (t, b) come from the constant table,
-// columns are coefficients. |C_b| <= 8 * 16 * 128 * 128 = 2^21 for up to 16
+// columns are coefficients. |C_b| <= 8 * 32 * 128 * 128 = 2^22 for up to 32
 // sources. A 32-row tile covers four targets; the host's row order puts all
 // eight C_b of targets 2h and 2h+1 in the accumulators of lane half h
 // (accumulator i = byte i % 8 of target 2h + i / 8).
@@ -436,7 +436,7 @@ __device__ __forceinline__ mx_v16i mx_step(const ulonglong2& a, const ulonglong2
 
 // The target whose partial sums start at accumulator BASE (0 or 8), as
 // lo = C0 + 2^8 C1 + 2^16 C2 + 2^24 C3 and hi = C4 + ... + 2^24 C7, exact
-// doubles below 2^46.1 in magnitude (the sum is lo + 2^32 hi).
+// doubles (each pair C + 2^8 C' below 2^30.1) below 2^46.1 in magnitude (the sum is lo + 2^32 hi).
 template <int BASE>
 __device__ __forceinline__ void mx_halves(const mx_v16i& acc, double& lo, double& hi) {
   const int a0 = acc[BASE + 0] + acc[BASE + 1] * 256, a1 = acc[BASE + 2] + acc[BASE + 3] * 256;
@@ -462,57 +462,94 @@ __device__ __forceinline__ uint64_t mx_fold_p(double lo, double hi, const LimbC&
          L.cadj;
 }
 
+// Columns of a workgroup: 64 (two column halves of 32, one per wave parity), or
+// 32 where the packed digits of 64 columns (2 KB nm R) would leave room for only
+// one workgroup of 8 waves on a CU. With 32 rows the registers do that anyway, and
+// it is 64 columns as long as they fit.
+constexpr int mx_cols(int logr, int nm) { return (nm << logr) <= (logr == 5 ? 64 : 40) ? 64 : 32; }
+constexpr int mx_lds(int logr, int nm) { return (nm << logr) * mx_cols(logr, nm) * 32; }
+
 // Phase 2 of the MFMA column kernels for one target group. A lane in half h
 // holds the partial sums of targets 2h and 2h + 1 of the group; each is
 // finished in its own pass (PASS 0: accumulators 0..7, PASS 1: 8..15), which
 // runs the nm MFMA steps of every row r over the packed digits yp
-// ([pairs][R][64] x 16 bytes) again, so that only one target's R values are
+// ([pairs][R][columns] x 16 bytes) again, so that only one target's R values are
 // live: for each row the fold mod t, then the forward column pass and, if
-// `st`, the store of the R rows. Q groups store raw words, P groups
+// `st`, the store of the R rows. Up to 8 rows both targets' values fit and PASS 2
+// finishes both from one run of the MFMA steps. Q groups store raw words, P groups
 // values below 2^64. The raised digits (and ModDown's t2) outgrow the caches,
 // so the stores are non-temporal (measured: 5% off the ModUp column kernel).
+template <bool QG>
+using mx_val = typename std::conditional<QG, double, uint64_t>::type;
+
+template <int LOGR, bool QG>
+__device__ __forceinline__ void mx_finish(const DevTables& tb, const LimbC& L, int t, mx_val<QG> (&z)[1 << LOGR],
+                                          bool st, uint64_t* o, size_t cc, int M) {
+  constexpr int R = 1 << LOGR;
+  if constexpr (QG)
+    sub_fwd<LOGR, -1, false>(arf(tb, L, t, false), z, 1u);
+  else
+    sub_fwd<LOGR, -1, false>(ari(tb, L, t, false), z, 1u);
+  if (st) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      uint64_t w;
+      if constexpr (QG)
+        w = d2raw(z[r]);
+      else
+        w = z[r];
+      __builtin_nontemporal_store(w, o + cc + (size_t)r * M);
+    }
+  }
+}
+
 template <int LOGR, bool QG, int NM, int PASS>
 __device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2* yp, const ulonglong2 (&cst)[NM],
-                                          int t0, int t1, bool st, uint64_t* o, size_t cc, int M) {
-  constexpr int R = 1 << LOGR;
+                                          int ta0, int ta1, int tb0, int tb1, bool sa, bool sb, uint64_t* oa,
+                                          uint64_t* ob, size_t cc, int M) {
+  constexpr int R = 1 << LOGR, C = mx_cols(LOGR, NM);
   const int lane = threadIdx.x & (TC - 1), h = lane >> 5;
-  const int ycol = ((threadIdx.x / TC) & 1) * 32 + (lane & 31);
-  const int t = h ? t1 : t0;
-  const LimbC& L = tb.limb[t];
-  const size_t N = (size_t)M * R;
-  using T = typename std::conditional<QG, double, uint64_t>::type;
-  T z[R];
-  const double q = L.qd, qi = L.qinv, r32 = L.r32_d;
-  int yo = h * R * TC + ycol;  // digit words of row r of step m: yp[yo + 2 m R TC + r TC]
+  const int ycol = (C == 64 ? ((threadIdx.x / TC) & 1) * 32 : 0) + (lane & 31);
+  const int ta = h ? ta1 : ta0, tc = h ? tb1 : tb0;
+  const LimbC& LA = tb.limb[ta];
+  const LimbC& LB = tb.limb[tc];
+  using T = mx_val<QG>;
+  T za[R], zb[R];
+  const double qa = LA.qd, qia = LA.qinv, r32a = LA.r32_d;
+  const double qb = LB.qd, qib = LB.qinv, r32b = LB.r32_d;
+  int yo = h * R * C + ycol;  // digit words of row r of step m: yp[yo + (2 m R + r) C]
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     mx_v16i acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-    for (int m = 0; m < NM; ++m) acc = mx_step(cst[m], yp[yo + (2 * m * R + r) * TC], acc);
+    for (int m = 0; m < NM; ++m) acc = mx_step(cst[m], yp[yo + (2 * m * R + r) * C], acc);
     double lo, hi;
-    mx_halves<8 * PASS>(acc, lo, hi);
-    if constexpr (QG)
-      z[r] = mx_fold_q(lo, hi, q, qi, r32);
-    else
-      z[r] = mx_fold_p(lo, hi, L);
+    if constexpr (PASS != 1) {
+      mx_halves<0>(acc, lo, hi);
+      if constexpr (QG)
+        za[r] = mx_fold_q(lo, hi, qa, qia, r32a);
+      else
+        za[r] = mx_fold_p(lo, hi, LA);
+    }
+    if constexpr (PASS != 0) {
+      mx_halves<8>(acc, lo, hi);
+      if constexpr (QG)
+        zb[r] = mx_fold_q(lo, hi, qb, qib, r32b);
+      else
+        zb[r] = mx_fold_p(lo, hi, LB);
+    }
     // One row at a time: this row's result is materialised here (the compiler
     // would otherwise sink the folds below the loop and keep every row's
     // accumulators live), and the next row's digit loads wait for it.
-    asm volatile("" : "+v"(z[r]), "+v"(yo));
+    if constexpr (PASS == 0)
+      asm volatile("" : "+v"(za[r]), "+v"(yo));
+    else if constexpr (PASS == 1)
+      asm volatile("" : "+v"(zb[r]), "+v"(yo));
+    else
+      asm volatile("" : "+v"(za[r]), "+v"(zb[r]), "+v"(yo));
   }
-  if constexpr (QG) {
-    sub_fwd<LOGR, -1, false>(ArF{q, qi, tb.twf_d + (size_t)t * N}, z, 1u);
-    if (st) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) __builtin_nontemporal_store(d2raw(z[r]), o + cc + (size_t)r * M);
-    }
-  } else {
-    sub_fwd<LOGR, -1, false>(ari(tb, L, t, false), z, 1u);
-    if (st) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) __builtin_nontemporal_store(z[r], o + cc + (size_t)r * M);
-    }
-  }
+  if constexpr (PASS != 1) mx_finish<LOGR, QG>(tb, LA, ta, za, sa, oa, cc, M);
+  if constexpr (PASS != 0) mx_finish<LOGR, QG>(tb, LB, tc, zb, sb, ob, cc, M);
 }
 
 // lt[4]: the group's four limbs (padding slots replaced by a stand-in limb,
@@ -526,27 +563,37 @@ __device__ __forceinline__ void mx_group(const DevTables& tb, const ulonglong2* 
   ulonglong2 cst[NM];
 #pragma unroll
   for (int m = 0; m < NM; ++m) cst[m] = cst_g[m * 64 + lane];
-  mx_target<LOGR, QG, NM, 0>(tb, yp, cst, lt[0], lt[2], sa, oa, cc, M);
-  mx_target<LOGR, QG, NM, 1>(tb, yp, cst, lt[1], lt[3], sb, ob, cc, M);
+  if constexpr (LOGR <= 3) {
+    mx_target<LOGR, QG, NM, 2>(tb, yp, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
+  } else {
+    mx_target<LOGR, QG, NM, 0>(tb, yp, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
+    mx_target<LOGR, QG, NM, 1>(tb, yp, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
+  }
 }
 
+// Waves per SIMD the MFMA column kernels are built for: 4 where the LDS holds two
+// workgroups and a lane's rows fit 128 registers.
+constexpr int mx_waves(int logr, int nm) { return logr <= 4 && mx_lds(logr, nm) <= 80 * 1024 ? 4 : 2; }
+
 // ModUp columns with the int8-MFMA BConv: same arguments and output as
-// k_modup_cols. Phase 1 (wave w: sources w, w + 8, ... < 4 nm): inverse
-// column pass and pre-scale as in k_modup_cols, canonical y packed into LDS
-// as [pair][R][64] x 16 bytes (pair p = sources 2p, 2p + 1; zero past the
-// digit's sources and for columns past M). Phase 2: wave w takes the column
-// half w % 2 (lane l works on column (w % 2) * 32 + l % 32 of the workgroup)
-// and the target groups w/2, w/2 + 4, ...: per digit the Q targets outside
+// k_modup_cols. Phase 1: inverse column pass and pre-scale as in k_modup_cols,
+// canonical y packed into LDS as [pair][R][columns] x 16 bytes (pair p = sources
+// 2p, 2p + 1; zero past the digit's sources and for columns past M); with 64
+// columns a wave takes one source at a time, with 32 one in each lane half.
+// Phase 2: with 64 columns wave w takes the column half w % 2 (lane l works on
+// column (w % 2) * 32 + l % 32 of the workgroup) and the target groups w/2,
+// w/2 + 4, ...; with 32 the groups w, w + 8, ...: per digit the Q targets outside
 // D_j in groups of four (in basis order), then the P targets.
 template <int LOGR, int NM>
-__global__ __launch_bounds__(CT, LOGR == 4 ? 4 : 1) void k_modup_cols_mx(DevTables tb, const uint64_t* t1, uint64_t* ext1, int j0,
+__global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_modup_cols_mx(DevTables tb, const uint64_t* t1, uint64_t* ext1, int j0,
                                                      int nslots, int slot_stride, int tgt0, int tgt1, int log_m) {
-  constexpr int R = 1 << LOGR;
+  constexpr int R = 1 << LOGR, C = mx_cols(LOGR, NM), SPW = TC / C;  // SPW: sources of a wave at a time
   extern __shared__ ulonglong2 yp[];
   const int M = 1 << log_m;
   const size_t N = (size_t)M * R;
   const int lane = threadIdx.x & (TC - 1), wv = threadIdx.x / TC;
-  const size_t c = (size_t)blockIdx.x * TC + lane;
+  const int col = lane & (C - 1);
+  const size_t c = (size_t)blockIdx.x * C + col;
   const bool live = c < (size_t)M;
   const int j = j0 + blockIdx.y;
   const int item = blockIdx.z;
@@ -555,7 +602,7 @@ __global__ __launch_bounds__(CT, LOGR == 4 ? 4 : 1) void k_modup_cols_mx(DevTabl
   const int na = min(lo + tb.alpha, ell) - lo;
   constexpr int nm = NM;  // = tb.up_nm
   uint64_t* yw = reinterpret_cast<uint64_t*>(yp);
-  for (int s = wv; s < 4 * nm; s += CW) {
+  for (int s = wv * SPW + lane / C; s < 4 * nm; s += CW * SPW) {
     uint64_t y[R];
     if (live && s < na) {
       const int i = lo + s;
@@ -573,17 +620,17 @@ __global__ __launch_bounds__(CT, LOGR == 4 ? 4 : 1) void k_modup_cols_mx(DevTabl
       for (int r = 0; r < R; ++r) y[r] = 0;
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) yw[((size_t)((s >> 1) * R + r) * TC + lane) * 2 + (s & 1)] = y[r];
+    for (int r = 0; r < R; ++r) yw[((size_t)((s >> 1) * R + r) * C + col) * 2 + (s & 1)] = y[r];
   }
   __syncthreads();
   const int h = lane >> 5;
-  const size_t cc = (size_t)blockIdx.x * TC + (wv & 1) * 32 + (lane & 31);
+  const size_t cc = (size_t)blockIdx.x * C + (C == 64 ? (wv & 1) * 32 : 0) + (lane & 31);
   const bool clive = cc < (size_t)M;
   const int slot = slot_stride ? j : 0;
   uint64_t* e = ext1 + ((size_t)item * nslots + slot) * (size_t)nl * N;
   const int nq = ell - na, nqg = (nq + 3) >> 2, ng = nqg + ((k + 3) >> 2);
   const ulonglong2* cst_j = reinterpret_cast<const ulonglong2*>(tb.up_mx) + (size_t)j * tb.up_ng * nm * 64;
-  for (int g = wv >> 1; g < ng; g += CW / 2) {
+  for (int g = wv / (C / 32); g < ng; g += CW / (C / 32)) {
     const bool qg = g < nqg;
     int tg[4];
     bool any = false;
@@ -826,27 +873,27 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_moddown_cols(DevTable
 }
 
 // ModDown columns with the int8-MFMA BConv: same arguments and output as
-// k_moddown_cols. Phase 1 (wave w: P limbs w, w + 8, ... < 4 nm): inverse
-// column pass of acc_P and the scale by N^-1 [(P/p_m)^-1]_{p_m} as in
-// k_moddown_cols, canonical y packed into LDS ([pair][R][64] x 16 bytes,
-// zero past the k sources and for columns past M). Phase 2: wave w takes the
-// column half w % 2 and the groups of four Q limbs w/2, w/2 + 4, ... that
-// meet [tgt0, tgt1); output t2 raw.
+// k_moddown_cols. Phase 1 (the P limbs in the place of k_modup_cols_mx's sources):
+// inverse column pass of acc_P and the scale by N^-1 [(P/p_m)^-1]_{p_m} as in
+// k_moddown_cols, canonical y packed into LDS ([pair][R][columns] x 16 bytes,
+// zero past the k sources and for columns past M). Phase 2: the groups of four Q
+// limbs that meet [tgt0, tgt1), shared out as in k_modup_cols_mx; output t2 raw.
 template <int LOGR, int NM>
-__global__ __launch_bounds__(CT, LOGR == 4 ? 4 : 1) void k_moddown_cols_mx(DevTables tb, const uint64_t* accp, uint64_t* t2, int tgt0,
+__global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_moddown_cols_mx(DevTables tb, const uint64_t* accp, uint64_t* t2, int tgt0,
                                                        int tgt1, int log_m) {
-  constexpr int R = 1 << LOGR;
+  constexpr int R = 1 << LOGR, C = mx_cols(LOGR, NM), SPW = TC / C;
   extern __shared__ ulonglong2 yp[];
   const int M = 1 << log_m;
   const size_t N = (size_t)M * R;
   const int lane = threadIdx.x & (TC - 1), wv = threadIdx.x / TC;
-  const size_t c = (size_t)blockIdx.x * TC + lane;
+  const int col = lane & (C - 1);
+  const size_t c = (size_t)blockIdx.x * C + col;
   const bool live = c < (size_t)M;
   const int comp = blockIdx.y, item = blockIdx.z;
   const int ell = tb.ell, nl = tb.nl, k = tb.k;
   constexpr int nm = NM;  // = tb.dn_nm
   uint64_t* yw = reinterpret_cast<uint64_t*>(yp);
-  for (int m = wv; m < 4 * nm; m += CW) {
+  for (int m = wv * SPW + lane / C; m < 4 * nm; m += CW * SPW) {
     uint64_t y[R];
     if (live && m < k) {
       const LimbC L = tb.limb[ell + m];
@@ -862,16 +909,15 @@ __global__ __launch_bounds__(CT, LOGR == 4 ? 4 : 1) void k_moddown_cols_mx(DevTa
       for (int r = 0; r < R; ++r) y[r] = 0;
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) yw[((size_t)((m >> 1) * R + r) * TC + lane) * 2 + (m & 1)] = y[r];
+    for (int r = 0; r < R; ++r) yw[((size_t)((m >> 1) * R + r) * C + col) * 2 + (m & 1)] = y[r];
   }
   __syncthreads();
   const int h = lane >> 5;
-  const size_t cc = (size_t)blockIdx.x * TC + (wv & 1) * 32 + (lane & 31);
+  const size_t cc = (size_t)blockIdx.x * C + (C == 64 ? (wv & 1) * 32 : 0) + (lane & 31);
   const bool clive = cc < (size_t)M;
   uint64_t* o = t2 + ((size_t)item * 2 + comp) * ell * N;
   const ulonglong2* cst = reinterpret_cast<const ulonglong2*>(tb.dn_mx);
-  for (int g = (wv >> 1) + ((tgt0 >> 2) & ~(CW / 2 - 1)); 4 * g < tgt1; g += CW / 2) {
-    if (4 * g + 4 <= tgt0) continue;
+  for (int g = (tgt0 >> 2) + wv / (C / 32); 4 * g < tgt1; g += CW / (C / 32)) {
     const int ta = 4 * g + 2 * h, tb2 = ta + 1;
     const bool sa = clive && ta >= tgt0 && ta < tgt1;
     const bool sb = clive && tb2 >= tgt0 && tb2 < tgt1;
@@ -1410,26 +1456,9 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_pblocks_inv(DevTables 
 
 // ------------------------------------------------------------ dispatching
 
-// LDS of an MFMA column workgroup: 2 nm pairs of 16-byte digit words per row and column.
-inline size_t mx_lds_bytes(int nm, int log_r) { return (size_t)nm * ((size_t)1 << log_r) * TC * 32; }
 
 template <template <int> class F, typename... A>
 hipError_t by_logr(int log_r, A... a) {
-  switch (log_r) {
-    case 0: return F<0>::run(a...);
-    case 1: return F<1>::run(a...);
-    case 2: return F<2>::run(a...);
-    case 3: return F<3>::run(a...);
-    case 4: return F<4>::run(a...);
-    case 5: return F<5>::run(a...);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-// The MFMA column kernels hold 2R values per lane: at most 32 rows (at 32 rows
-// with two waves per SIMD).
-template <template <int> class F, typename... A>
-hipError_t by_logr_mx(int log_r, A... a) {
   switch (log_r) {
     case 0: return F<0>::run(a...);
     case 1: return F<1>::run(a...);
@@ -1497,8 +1526,8 @@ hipError_t by_logm_k3(int log_m, long wgs, A... a) {
   }
 }
 
-dim3 col_grid(int log_m, int y, int z) {
-  return dim3((unsigned)(((1 << log_m) + TC - 1) / TC), (unsigned)y, (unsigned)z);
+dim3 col_grid(int log_m, int y, int z, int cols = TC) {
+  return dim3((unsigned)(((1 << log_m) + cols - 1) / cols), (unsigned)y, (unsigned)z);
 }
 
 template <int LOGM, int LOGE>
@@ -1562,25 +1591,33 @@ struct ModupCols {
     return hipGetLastError();
   }
 };
-template <int LOGR, int NM>
-hipError_t modup_cols_mx(const DevTables& tb, const uint64_t* t1, uint64_t* ext1, int j0, int nj, int nslots,
-                         int slot_stride, int tgt0, int tgt1, int items, int log_m, hipStream_t s) {
-  allow_lds<k_modup_cols_mx<LOGR, NM>>();
-  k_modup_cols_mx<LOGR, NM><<<col_grid(log_m, nj, items), dim3(CT), mx_lds_bytes(NM, LOGR), s>>>(
-      tb, t1, ext1, j0, nslots, slot_stride, tgt0, tgt1, log_m);
-  return hipGetLastError();
+// Steps (of four sources) an MFMA column kernel is built for: 8, or fewer where
+// its digits would not fit 160 KB of LDS.
+constexpr int mx_max_nm(int logr) { return logr <= 4 ? 8 : 4; }
+
+// F<LOGR, nm>::run for a runtime nm.
+template <template <int, int> class F, int LOGR, int NM = 1, typename... A>
+hipError_t by_nm(int nm, A... a) {
+  if constexpr (NM > mx_max_nm(LOGR))
+    return hipErrorInvalidValue;
+  else
+    return nm == NM ? F<LOGR, NM>::run(a...) : by_nm<F, LOGR, NM + 1>(nm, a...);
 }
+template <int LOGR, int NM>
+struct ModupColsMxN {
+  static hipError_t run(const DevTables& tb, const uint64_t* t1, uint64_t* ext1, int j0, int nj, int nslots,
+                        int slot_stride, int tgt0, int tgt1, int items, int log_m, hipStream_t s) {
+    allow_lds<k_modup_cols_mx<LOGR, NM>>();
+    k_modup_cols_mx<LOGR, NM><<<col_grid(log_m, nj, items, mx_cols(LOGR, NM)), dim3(CT), mx_lds(LOGR, NM), s>>>(
+        tb, t1, ext1, j0, nslots, slot_stride, tgt0, tgt1, log_m);
+    return hipGetLastError();
+  }
+};
 template <int LOGR>
 struct ModupColsMx {
   template <typename... A>
   static hipError_t run(const DevTables& tb, A... a) {
-    switch (tb.up_nm) {
-      case 1: return modup_cols_mx<LOGR, 1>(tb, a...);
-      case 2: return modup_cols_mx<LOGR, 2>(tb, a...);
-      case 3: return modup_cols_mx<LOGR, 3>(tb, a...);
-      case 4: return modup_cols_mx<LOGR, 4>(tb, a...);
-      default: return hipErrorInvalidValue;
-    }
+    return by_nm<ModupColsMxN, LOGR>(tb.up_nm, tb, a...);
   }
 };
 template <int LOGM, int LOGE>
@@ -1621,24 +1658,20 @@ struct ModdownCols {
   }
 };
 template <int LOGR, int NM>
-hipError_t moddown_cols_mx(const DevTables& tb, const uint64_t* accp, uint64_t* t2, int tgt0, int tgt1, int items,
-                           int log_m, hipStream_t s) {
-  allow_lds<k_moddown_cols_mx<LOGR, NM>>();
-  k_moddown_cols_mx<LOGR, NM><<<col_grid(log_m, 2, items), dim3(CT), mx_lds_bytes(NM, LOGR), s>>>(
-      tb, accp, t2, tgt0, tgt1, log_m);
-  return hipGetLastError();
-}
+struct ModdownColsMxN {
+  static hipError_t run(const DevTables& tb, const uint64_t* accp, uint64_t* t2, int tgt0, int tgt1, int items,
+                        int log_m, hipStream_t s) {
+    allow_lds<k_moddown_cols_mx<LOGR, NM>>();
+    k_moddown_cols_mx<LOGR, NM><<<col_grid(log_m, 2, items, mx_cols(LOGR, NM)), dim3(CT), mx_lds(LOGR, NM), s>>>(
+        tb, accp, t2, tgt0, tgt1, log_m);
+    return hipGetLastError();
+  }
+};
 template <int LOGR>
 struct ModdownColsMx {
   template <typename... A>
   static hipError_t run(const DevTables& tb, A... a) {
-    switch (tb.dn_nm) {
-      case 1: return moddown_cols_mx<LOGR, 1>(tb, a...);
-      case 2: return moddown_cols_mx<LOGR, 2>(tb, a...);
-      case 3: return moddown_cols_mx<LOGR, 3>(tb, a...);
-      case 4: return moddown_cols_mx<LOGR, 4>(tb, a...);
-      default: return hipErrorInvalidValue;
-    }
+    return by_nm<ModdownColsMxN, LOGR>(tb.dn_nm, tb, a...);
   }
 };
 template <int LOGM, int LOGE>
@@ -1731,10 +1764,21 @@ struct PBlocksInv {
 // columns per workgroup, 8 bytes each, at most 160 KB).
 int stage_cap(int count, int log_r) { return (size_t)count * ((size_t)1 << log_r) * 64 * 8 <= 160 * 1024 ? 1 : 0; }
 
+// What KS_PLAN_MFMA_BCONV accepts: at most 16 sources, and the digits of 64
+// columns within 160 KB of LDS.
 int mx_ok(const DevTables& tb, int log_r) {
-  // at most 16 sources (the partial-sum bound), 32 rows per column (registers), LDS
-  return tb.up_nm <= 4 && tb.dn_nm <= 4 && log_r <= 5 && mx_lds_bytes(tb.up_nm, log_r) <= 160 * 1024 &&
-         mx_lds_bytes(tb.dn_nm, log_r) <= 160 * 1024;
+  auto fits = [log_r](int nm) { return nm <= 4 && (nm << log_r) * 64 * 32 <= 160 * 1024; };
+  return log_r <= 5 && fits(tb.up_nm) && fits(tb.dn_nm);
+}
+
+// Whether a column pass whose BConv has `count` sources (nm steps of four) runs it
+// on the matrix cores without being asked to: wherever the kernel exists, from
+// 4 sources on. The scalar products grow with the sources, the matrix form's
+// folds do not: whole KeySwitch, scalar / matrix, at batch 4 and the best split,
+// (8, 2^16, 16), 2 sources, 340 / 370 us; (8, 2^16, 24), 3: 476 / 482;
+// (8, 2^16, 32), 4: 643 / 591; (2, 2^17, 50), one ciphertext, 25: 852 / 567.
+inline bool mx_auto(int count, int nm, int log_r) {
+  return count >= 4 && nm <= mx_max_nm(log_r) && mx_lds(log_r, nm) <= 160 * 1024;
 }
 
 hipError_t launch_ntt(const DevTables& tb, int log_r, uint64_t* x, int first, int nlimbs, int items, hipStream_t s) {
@@ -1766,8 +1810,8 @@ hipError_t launch_eval_blocks(const DevTables& tb, int log_r, EvalIn ev, uint64_
 
 hipError_t launch_modup_cols(const DevTables& tb, int log_r, const uint64_t* t1, uint64_t* ext1, int j0, int nj,
                              int nslots, int slot_stride, int tgt0, int tgt1, int items, int mfma, hipStream_t s) {
-  if (mfma)
-    return by_logr_mx<ModupColsMx>(log_r, tb, t1, ext1, j0, nj, nslots, slot_stride, tgt0, tgt1, items,
+  if (mfma || mx_auto(tb.alpha < tb.ell ? tb.alpha : tb.ell, tb.up_nm, log_r))
+    return by_logr<ModupColsMx>(log_r, tb, t1, ext1, j0, nj, nslots, slot_stride, tgt0, tgt1, items,
                                 tb.log_n - log_r, s);
   return by_logr<ModupCols>(log_r, tb, t1, ext1, j0, nj, nslots, slot_stride, tgt0, tgt1, items, tb.log_n - log_r, s);
 }
@@ -1790,7 +1834,8 @@ hipError_t launch_moddown_km_blocks(const DevTables& tb, int log_r, const uint64
 
 hipError_t launch_moddown_cols(const DevTables& tb, int log_r, const uint64_t* accp, uint64_t* t2, int tgt0,
                                int tgt1, int items, int mfma, hipStream_t s) {
-  if (mfma) return by_logr_mx<ModdownColsMx>(log_r, tb, accp, t2, tgt0, tgt1, items, tb.log_n - log_r, s);
+  if (mfma || mx_auto(tb.k, tb.dn_nm, log_r))
+    return by_logr<ModdownColsMx>(log_r, tb, accp, t2, tgt0, tgt1, items, tb.log_n - log_r, s);
   return by_logr<ModdownCols>(log_r, tb, accp, t2, tgt0, tgt1, items, tb.log_n - log_r, s);
 }
 
