@@ -38,8 +38,6 @@ struct LimbC {
   uint64_t q;
   uint64_t nq;         // 2^64 - q
   uint64_t delta;      // 2^60 - q (P primes; below 2^29)
-  uint64_t mont_ninv;  // -q^-1 mod 2^64
-  uint64_t r2;         // 2^128 mod q
   uint64_t ninv, ninv_s;
   uint64_t red_s;      // floor(2^64 / q): Shoup companion of 1
   double qd;           // q as a double (exact for the Q primes)

@@ -240,9 +240,6 @@ void build_tables(const HostParams& hp, std::vector<uint64_t>& blob, DevTables& 
     L.q = q;
     L.nq = ~q + 1;
     L.delta = ((uint64_t)1 << 60) - q;
-    L.mont_ninv = mont_neg_inv(q);
-    const uint64_t r1 = (uint64_t)(((u128)1 << 64) % q);
-    L.r2 = host_mulmod(r1, r1, q);
     L.ninv = inv_prime(n % q, q);
     L.ninv_s = shoup(L.ninv, q);
     L.red_s = shoup(1, q);

@@ -482,10 +482,23 @@ constexpr int mx_lds(int logr, int nm) { return (nm << logr) * mx_cols(logr, nm)
 template <bool QG>
 using mx_val = typename std::conditional<QG, double, uint64_t>::type;
 
-template <int LOGR, bool QG>
+// CONV: the conversion alone (ks_bconv): no transform, canonical words.
+template <int LOGR, bool QG, bool CONV>
 __device__ __forceinline__ void mx_finish(const DevTables& tb, const LimbC& L, int t, mx_val<QG> (&z)[1 << LOGR],
                                           bool st, uint64_t* o, size_t cc, int M) {
   constexpr int R = 1 << LOGR;
+  if constexpr (CONV) {
+    if (st) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if constexpr (QG)
+          o[cc + (size_t)r * M] = f_canon(z[r], L.qd, L.qinv);
+        else
+          o[cc + (size_t)r * M] = p_canon(z[r], L.q, (uint32_t)L.delta);
+      }
+    }
+    return;
+  }
   if constexpr (QG)
     sub_fwd<LOGR, -1, false>(arf(tb, L, t, false), z, 1u);
   else
@@ -503,7 +516,7 @@ __device__ __forceinline__ void mx_finish(const DevTables& tb, const LimbC& L, i
   }
 }
 
-template <int LOGR, bool QG, int NM, int PASS>
+template <int LOGR, bool QG, int NM, int PASS, bool CONV>
 __device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2* yp, const ulonglong2 (&cst)[NM],
                                           int ta0, int ta1, int tb0, int tb1, bool sa, bool sb, uint64_t* oa,
                                           uint64_t* ob, size_t cc, int M) {
@@ -548,14 +561,14 @@ __device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2*
     else
       asm volatile("" : "+v"(za[r]), "+v"(zb[r]), "+v"(yo));
   }
-  if constexpr (PASS != 1) mx_finish<LOGR, QG>(tb, LA, ta, za, sa, oa, cc, M);
-  if constexpr (PASS != 0) mx_finish<LOGR, QG>(tb, LB, tc, zb, sb, ob, cc, M);
+  if constexpr (PASS != 1) mx_finish<LOGR, QG, CONV>(tb, LA, ta, za, sa, oa, cc, M);
+  if constexpr (PASS != 0) mx_finish<LOGR, QG, CONV>(tb, LB, tc, zb, sb, ob, cc, M);
 }
 
 // lt[4]: the group's four limbs (padding slots replaced by a stand-in limb,
 // wave-uniform); lane half h finishes targets lt[2h] (stored if sa, at oa)
 // and lt[2h + 1] (if sb, at ob).
-template <int LOGR, bool QG, int NM>
+template <int LOGR, bool QG, int NM, bool CONV = false>
 __device__ __forceinline__ void mx_group(const DevTables& tb, const ulonglong2* yp, const ulonglong2* cst_g,
                                          const int (&lt)[4], bool sa, bool sb, uint64_t* oa, uint64_t* ob,
                                          size_t cc, int M) {
@@ -564,10 +577,10 @@ __device__ __forceinline__ void mx_group(const DevTables& tb, const ulonglong2* 
 #pragma unroll
   for (int m = 0; m < NM; ++m) cst[m] = cst_g[m * 64 + lane];
   if constexpr (LOGR <= 3) {
-    mx_target<LOGR, QG, NM, 2>(tb, yp, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
+    mx_target<LOGR, QG, NM, 2, CONV>(tb, yp, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
   } else {
-    mx_target<LOGR, QG, NM, 0>(tb, yp, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
-    mx_target<LOGR, QG, NM, 1>(tb, yp, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
+    mx_target<LOGR, QG, NM, 0, CONV>(tb, yp, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
+    mx_target<LOGR, QG, NM, 1, CONV>(tb, yp, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
   }
 }
 
@@ -1365,6 +1378,73 @@ __global__ void k_bconv(DevTables tb, const uint64_t* src, uint64_t* dst, int se
   dst[((size_t)item * nd + u) * N + x] = reduce2(mul_shoup(z, 1, L.red_s, L.q), L.q);
 }
 
+// ks_bconv on the matrix cores, for the numbers of sources the column kernels take
+// them for: a workgroup converts BC_R rows of 64 (32 from 6 steps on) of the N
+// coefficients (rows N / BC_R apart, which keeps every access to consecutive
+// words) to the target groups g with g mod gridDim.z = blockIdx.z. Phase 1 scales
+// each source word once and packs its digits; the scalar kernel does that again for
+// every target (114 us for 8 sources to 32 targets of 4 x 2^16 coefficients).
+constexpr int BC_LOGR = 3, BC_R = 1 << BC_LOGR;
+
+template <int NM>
+__global__ __launch_bounds__(CT, mx_waves(BC_LOGR, NM)) void k_bconv_mx(DevTables tb, const uint64_t* src,
+                                                                        uint64_t* dst, int set) {
+  constexpr int C = mx_cols(BC_LOGR, NM), SPW = TC / C;
+  extern __shared__ ulonglong2 yp[];
+  const int M = 1 << (tb.log_n - BC_LOGR);
+  const size_t N = (size_t)M * BC_R;
+  const int lane = threadIdx.x & (TC - 1), wv = threadIdx.x / TC, col = lane & (C - 1);
+  const size_t c = (size_t)blockIdx.x * C + col;
+  const bool live = c < (size_t)M;
+  const int item = blockIdx.y, ell = tb.ell, k = tb.k;
+  const int lo = set < 0 ? ell : set * tb.alpha;
+  const int ns = (set < 0 ? tb.nl : min(lo + tb.alpha, ell)) - lo;
+  uint64_t* yw = reinterpret_cast<uint64_t*>(yp);
+  for (int s = wv * SPW + lane / C; s < 4 * NM; s += CW * SPW) {
+    uint64_t y[BC_R];
+#pragma unroll
+    for (int r = 0; r < BC_R; ++r) y[r] = 0;
+    if (live && s < ns) {
+      const uint64_t q = tb.limb[lo + s].q;
+      const uint64_t* hinv = set < 0 ? tb.dn_hinv + 2 * s : tb.up_hinv + 2 * (lo + s);
+      const uint64_t w = hinv[0], ws = hinv[1];
+      const uint64_t* a = src + ((size_t)item * ns + s) * N + c;
+#pragma unroll
+      for (int r = 0; r < BC_R; ++r) y[r] = a[(size_t)r * M];
+#pragma unroll
+      for (int r = 0; r < BC_R; ++r) y[r] = mx_pack(reduce2(mul_shoup(y[r], w, ws, q), q));
+    }
+#pragma unroll
+    for (int r = 0; r < BC_R; ++r) yw[((size_t)((s >> 1) * BC_R + r) * C + col) * 2 + (s & 1)] = y[r];
+  }
+  __syncthreads();
+  const int h = lane >> 5;
+  const size_t cc = (size_t)blockIdx.x * C + (C == 64 ? (wv & 1) * 32 : 0) + (lane & 31);
+  const bool clive = cc < (size_t)M;
+  const int nq = set < 0 ? ell : ell - ns, nqg = (nq + 3) >> 2, ng = nqg + (set < 0 ? 0 : (k + 3) >> 2);
+  uint64_t* o = dst + (size_t)item * (set < 0 ? ell : tb.nl - ns) * N;
+  const ulonglong2* cst = set < 0 ? reinterpret_cast<const ulonglong2*>(tb.dn_mx)
+                                  : reinterpret_cast<const ulonglong2*>(tb.up_mx) + (size_t)set * tb.up_ng * NM * 64;
+  for (int g = (wv / (C / 32)) * gridDim.z + blockIdx.z; g < ng; g += (CW / (C / 32)) * gridDim.z) {
+    const bool qg = g < nqg;
+    // target tau of the group is output row u; the last group of each kind may be short
+    const int u0 = qg ? 4 * g : nq + 4 * (g - nqg), cnt = min(4, qg ? nq - 4 * g : k - 4 * (g - nqg));
+    int lt[4];
+#pragma unroll
+    for (int tau = 0; tau < 4; ++tau) {
+      const int u = u0 + min(tau, cnt - 1);
+      lt[tau] = set < 0 || u < lo ? u : u + ns;
+    }
+    const bool sa = clive && 2 * h < cnt, sb = clive && 2 * h + 1 < cnt;
+    uint64_t* oa = o + (size_t)(u0 + (sa ? 2 * h : 0)) * N;
+    uint64_t* ob = o + (size_t)(u0 + (sb ? 2 * h + 1 : 0)) * N;
+    if (qg)
+      mx_group<BC_LOGR, true, NM, true>(tb, yp, cst + (size_t)g * NM * 64, lt, sa, sb, oa, ob, cc, M);
+    else
+      mx_group<BC_LOGR, false, NM, true>(tb, yp, cst + (size_t)g * NM * 64, lt, sa, sb, oa, ob, cc, M);
+  }
+}
+
 // ------------------------------------------------- HMUL and HROT (element-wise)
 
 // HMUL's tensor product over the Q limbs: for ciphertexts a, b
@@ -1416,20 +1496,89 @@ __global__ __launch_bounds__(256) void k_add_q(DevTables tb, uint64_t* out, cons
   out[r] = v >= q ? v - q : v;
 }
 
-// ks_keymult: element-wise over acc [items][2][nl][N], integer arithmetic.
-__global__ void k_keymult(DevTables tb, const uint64_t* ext, const uint64_t* evk, uint64_t* acc) {
+// ks_keymult: element-wise over acc [items][2][nl][N]. A thread takes 2 elements
+// (256 apart) of one limb for IT items and both components, so that ext is read
+// once and a key word once for IT items: it is bound by those bytes (420 MB for
+// two items of (4, 2^16, 32); one item and component a thread read 588 MB). Q limbs
+// on FP64 (canonical operands: each product within 0.88q), P limbs with p_mul.
+// Grid: (ceil(N / 512), nl, ceil(items / IT)).
+template <int IT>
+__global__ __launch_bounds__(256) void k_keymult(DevTables tb, const uint64_t* ext, const uint64_t* evk,
+                                                 uint64_t* acc, int items) {
+  constexpr int E = 2;
   const size_t N = (size_t)1 << tb.log_n;
-  const size_t x = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= N) return;
-  const int t = blockIdx.y % tb.nl, c = blockIdx.y / tb.nl, item = blockIdx.z;
+  const size_t x0 = (size_t)blockIdx.x * (256 * E) + threadIdx.x;
+  const int t = blockIdx.y, i0 = blockIdx.z * IT, nl = tb.nl, ndig = tb.ndig;
   const LimbC L = tb.limb[t];
-  uint64_t s = 0;
-  for (int j = 0; j < tb.ndig; ++j) {
-    s += mont_mul(ext[(((size_t)item * tb.ndig + j) * tb.nl + t) * N + x], evk[key_row(tb, j, c, t) * N + x],
-                  L.q, L.mont_ninv);
-    s = s >= 2 * L.q ? s - 2 * L.q : s;
+  const uint32_t delta = (uint32_t)L.delta;
+  // words past the end of a small limb or batch are read from its first word or item, and not stored
+  size_t x[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) x[e] = x0 + 256 * e < N ? x0 + 256 * e : 0;
+  const bool isq = t < tb.ell;
+  double sq[IT][2][E];
+  uint64_t sp[IT][2][E];
+#pragma unroll
+  for (int i = 0; i < IT; ++i)
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      sq[i][0][e] = sq[i][1][e] = 0.0;
+      sp[i][0][e] = sp[i][1][e] = 0;
+    }
+  auto load = [&](int j, uint64_t (&kw)[2][E], uint64_t (&w)[IT][E]) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const uint64_t* key = evk + key_row(tb, j, c, t) * N;
+#pragma unroll
+      for (int e = 0; e < E; ++e) kw[c][e] = key[x[e]];
+    }
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      const uint64_t* a = ext + (((size_t)(i0 + i < items ? i0 + i : i0) * ndig + j) * nl + t) * N;
+#pragma unroll
+      for (int e = 0; e < E; ++e) w[i][e] = a[x[e]];
+    }
+  };
+  uint64_t kw[2][E], w[IT][E];
+  if (isq) {
+    for (int j = 0; j < ndig; ++j) {
+      load(j, kw, w);
+#pragma unroll
+      for (int i = 0; i < IT; ++i)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            sq[i][c][e] += f_mul(u2d(w[i][e]), u2d(kw[c][e]), L.qd, L.qinv);
+            if ((j & 7) == 7) sq[i][c][e] = f_red(sq[i][c][e], L.qd, L.qinv);
+          }
+    }
+  } else {
+    for (int j = 0; j < ndig; ++j) {
+      load(j, kw, w);
+#pragma unroll
+      for (int i = 0; i < IT; ++i)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            sp[i][c][e] += p_mul(w[i][e], kw[c][e], delta);
+            if ((j & 7) == 7) sp[i][c][e] = p_red(sp[i][c][e], delta);
+          }
+    }
   }
-  acc[(((size_t)item * 2 + c) * tb.nl + t) * N + x] = reduce2(mont_mul(s, L.r2, L.q, L.mont_ninv), L.q);
+#pragma unroll
+  for (int i = 0; i < IT; ++i) {
+    if (i0 + i >= items) break;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      uint64_t* a = acc + (((size_t)(i0 + i) * 2 + c) * nl + t) * N;
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (x0 + 256 * e < N)
+          a[x[e]] = isq ? f_canon_wide(sq[i][c][e], L.qd, L.qinv) : p_canon(sp[i][c][e], L.q, delta);
+    }
+  }
 }
 
 // ks_moddown, first step: inverse block pass of the P limbs of acc
@@ -1674,6 +1823,18 @@ struct ModdownColsMx {
     return by_nm<ModdownColsMxN, LOGR>(tb.dn_nm, tb, a...);
   }
 };
+template <int LOGR, int NM>
+struct BconvMxN {
+  static hipError_t run(const DevTables& tb, const uint64_t* src, int set, uint64_t* dst, int items, hipStream_t s) {
+    allow_lds<k_bconv_mx<NM>>();
+    dim3 g = col_grid(tb.log_n - BC_LOGR, items, 1, mx_cols(BC_LOGR, NM));
+    // few workgroups: the target groups are shared out over up to 4 of them
+    // (each scales the sources again), until there are two for every CU
+    while (g.z < 4 && g.x * g.y * g.z < 512) g.z *= 2;
+    k_bconv_mx<NM><<<g, dim3(CT), mx_lds(BC_LOGR, NM), s>>>(tb, src, dst, set);
+    return hipGetLastError();
+  }
+};
 template <int LOGM, int LOGE>
 struct ModdownBlocks {
   static hipError_t run(const DevTables& tb, const uint64_t* t2, const uint64_t* acc, uint64_t* out, int tgt0,
@@ -1882,6 +2043,9 @@ hipError_t launch_bconv(const DevTables& tb, const uint64_t* src, int set, uint6
     const int hi = lo + tb.alpha < tb.ell ? lo + tb.alpha : tb.ell;
     nd = tb.nl - (hi - lo);
   }
+  const int ns = tb.nl - (set < 0 ? tb.ell : nd);
+  const int nm = set < 0 ? tb.dn_nm : tb.up_nm;
+  if (mx_auto(ns, nm, BC_LOGR)) return by_nm<BconvMxN, BC_LOGR>(nm, tb, src, set, dst, items, s);
   k_bconv<<<dim3((n + 255) / 256, nd, items), dim3(256), 0, s>>>(tb, src, dst, set);
   return hipGetLastError();
 }
@@ -2025,8 +2189,11 @@ hipError_t launch_copy_rate(int kind, int nt, int blocks, const uint64_t* src, u
 
 hipError_t launch_keymult(const DevTables& tb, const uint64_t* ext, const uint64_t* evk, uint64_t* acc, int items,
                           hipStream_t s) {
-  const unsigned n = 1u << tb.log_n;
-  k_keymult<<<dim3((n + 255) / 256, 2 * tb.nl, items), dim3(256), 0, s>>>(tb, ext, evk, acc);
+  const unsigned n = 1u << tb.log_n, gx = (n + 511) / 512;
+  if (items == 1)
+    k_keymult<1><<<dim3(gx, tb.nl, 1), dim3(256), 0, s>>>(tb, ext, evk, acc, items);
+  else
+    k_keymult<2><<<dim3(gx, tb.nl, (items + 1) / 2), dim3(256), 0, s>>>(tb, ext, evk, acc, items);
   return hipGetLastError();
 }
 

@@ -7,10 +7,11 @@ each of those lines (3 / 4 sources, 16 / 17, 32 / 33; 2, 3 and 5 to 8 steps of
 four at 8 to 32 rows), with short last digits and levels below a digit, against
 the oracle bit for bit.
 """
+import numpy as np
 import pytest
 
 import oracle
-from synth import ciphertext_batch, uniform_key
+from synth import ciphertext_batch, uniform_key, uniform_residues
 
 from gpu_util import dev, empty, first_mismatch, host
 
@@ -57,3 +58,39 @@ def test_levels_below_and_across_a_digit(level):
         G.keyswitch(dev(d), dev(evk), out, 1, G.workspace(1, plan), plan)
         mm = first_mismatch(host(out), ref)
         assert mm is None, f"level {level} {plan}: first mismatch {mm}"
+
+
+@pytest.mark.parametrize("dnum,log_n,ell,batch", [
+    (1, 3, 4, 2), (2, 9, 8, 3), (2, 10, 33, 1), (1, 11, 32, 1), (1, 9, 33, 1), (3, 12, 13, 5)])
+def test_bconv_by_number_of_sources(dnum, log_n, ell, batch):
+    import paper_2603_16692_amd as ks
+    G, P = ks.KsParams(dnum, log_n, ell), oracle.Params(dnum, log_n, ell)
+    for j in list(range(P.ndig)) + [ks.KS_SET_P]:
+        mods = P.p if j < 0 else [P.moduli[i] for i in P.digit(j)]
+        x = np.stack([uniform_residues(50 + b + 7 * j, mods, P.n) for b in range(batch)])
+        x[0, :, ::5] = 0
+        x[0, :, 1::5] = np.array(mods, dtype=np.uint64)[:, None] - np.uint64(1)
+        ref = oracle.bconv(P, j, x, batch)
+        out = empty(ref.shape)
+        G.bconv(dev(x), j, out, batch)
+        mm = first_mismatch(host(out), ref)
+        assert mm is None, f"set {j}: first mismatch {mm}"
+
+
+# one item and two a thread, a last odd item, limbs shorter than a workgroup's
+# 512 elements, more digits than a sum holds unfolded
+@pytest.mark.parametrize("dnum,log_n,ell,batch", [(2, 3, 4, 3), (3, 8, 5, 1), (11, 9, 11, 2), (9, 10, 9, 5)])
+def test_keymult_shapes(dnum, log_n, ell, batch):
+    import paper_2603_16692_amd as ks
+    G, P = ks.KsParams(dnum, log_n, ell), oracle.Params(dnum, log_n, ell)
+    ext = np.stack([[uniform_residues(70 + b * P.ndig + j, P.moduli, P.n) for j in range(P.ndig)]
+                    for b in range(batch)])
+    top = np.array(P.moduli, dtype=np.uint64)[:, None] - np.uint64(1)
+    ext[..., ::3] = top
+    evk = uniform_key(P.moduli, P.n, P.ndig)
+    evk[..., ::2] = top
+    ref = oracle.keymult(P, ext, evk, batch)
+    acc = empty(ref.shape)
+    G.keymult(dev(ext), dev(evk), acc, batch)
+    mm = first_mismatch(host(acc), ref)
+    assert mm is None, f"first mismatch {mm}"
