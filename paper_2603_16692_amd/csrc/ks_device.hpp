@@ -206,7 +206,10 @@ struct Tw {
   uint64_t w, ws;
 };
 
+// UNI: idx is the same for the whole wavefront (a scalar load).
+template <bool UNI>
 __device__ __forceinline__ Tw load_tw(const uint64_t* table, uint32_t idx) {
+  if constexpr (UNI) return Tw{ldc(table + 2 * (size_t)idx), ldc(table + 2 * (size_t)idx + 1)};
   const ulonglong2 v = reinterpret_cast<const ulonglong2*>(table)[idx];
   return Tw{v.x, v.y};
 }
@@ -228,17 +231,20 @@ struct ArI {
   uint64_t q, nq;
   uint32_t delta;
   const uint64_t* tw;
+  using TwT = Tw;
+  template <bool UNI>
+  __device__ __forceinline__ TwT twiddle(uint32_t idx) const {
+    return load_tw<UNI>(tw, idx);
+  }
   template <bool RED>
-  __device__ __forceinline__ void fwd(T& X, T& Y, uint32_t idx) const {
-    const Tw t = load_tw(tw, idx);
+  __device__ __forceinline__ void fwd(T& X, T& Y, const TwT& t) const {
     const uint64_t x = RED ? p_red(X, delta) : X;
     const uint64_t v = mul_shoup_lazy(Y, t.w, t.ws, nq);
     X = x + v;
     Y = x + 4 * q - v;
   }
   template <bool RED>
-  __device__ __forceinline__ void inv(T& X, T& Y, uint32_t idx) const {
-    const Tw t = load_tw(tw, idx);
+  __device__ __forceinline__ void inv(T& X, T& Y, const TwT& t) const {
     const uint64_t s = X + Y, d = X + 8 * q - Y;
     X = RED ? p_red(s, delta) : s;
     Y = mul_shoup_lazy(d, t.w, t.ws, nq);
@@ -268,11 +274,17 @@ struct ArI {
 struct ArF {
   using T = double;
   double q, qinv;
-  const double* tw;
+  const double* tw;   // the table, or a block's staged copy of it
+  const double* ctw;  // the table, read where the whole wavefront takes one twiddle (UNI)
+  using TwT = double;
+  template <bool UNI>
+  __device__ __forceinline__ TwT twiddle(uint32_t idx) const {
+    if constexpr (UNI) return ldc(ctw + idx);
+    return tw[idx];
+  }
   // RED: X is first reduced to |X| <= q/2 + 2.
   template <bool RED>
-  __device__ __forceinline__ void fwd(T& X, T& Y, uint32_t idx) const {
-    const double w = tw[idx];
+  __device__ __forceinline__ void fwd(T& X, T& Y, TwT w) const {
     const double x = RED ? f_red(X, q, qinv) : X;
     const double v = f_mul(Y, w, q, qinv);
     X = x + v;
@@ -280,8 +292,7 @@ struct ArF {
   }
   // RED: the sum is reduced.
   template <bool RED>
-  __device__ __forceinline__ void inv(T& X, T& Y, uint32_t idx) const {
-    const double w = tw[idx];
+  __device__ __forceinline__ void inv(T& X, T& Y, TwT w) const {
     const double s = X + Y, d = X - Y;
     X = RED ? f_red(s, q, qinv) : s;
     Y = f_mul(d, w, q, qinv);
@@ -303,40 +314,61 @@ struct ArF {
 // PS.. are stored group-major, entry (p << rho) + g of stage PS + rho at
 // 2^(PS + rho) + (g << PS) + p, so that the lanes of a wave (consecutive p)
 // read consecutive words.
-template <int K, int PS = -1, bool RED0 = true, class Ar>
-__device__ __forceinline__ void sub_fwd(const Ar& A, typename Ar::T* x, uint32_t base) {
+//
+// The stages themselves, the twiddle of stage rho and group g given by tw(rho, g):
+template <int K, bool RED0 = true, class Ar, class F>
+__device__ __forceinline__ void sub_fwd_by(const Ar& A, typename Ar::T* x, F tw) {
 #pragma unroll
   for (int rho = 0; rho < K; ++rho) {
     const int dist = 1 << (K - 1 - rho);
 #pragma unroll
     for (int j = 0; j < (1 << K); ++j) {
       if (j & dist) continue;
-      const uint32_t g = (uint32_t)(j >> (K - rho));
-      const uint32_t idx = PS < 0 ? (base << rho) + g
-                                  : base + ((1u << (PS + rho)) - (1u << PS)) + (g << (PS < 0 ? 0 : PS));
+      const typename Ar::TwT w = tw(rho, (uint32_t)(j >> (K - rho)));
       if (Ar::fwd_red(rho, RED0))
-        A.template fwd<true>(x[j], x[j + dist], idx);
+        A.template fwd<true>(x[j], x[j + dist], w);
       else
-        A.template fwd<false>(x[j], x[j + dist], idx);
+        A.template fwd<false>(x[j], x[j + dist], w);
     }
   }
 }
-
-template <int K, class Ar>
-__device__ __forceinline__ void sub_inv(const Ar& A, typename Ar::T* x, uint32_t base) {
+template <int K, class Ar, class F>
+__device__ __forceinline__ void sub_inv_by(const Ar& A, typename Ar::T* x, F tw) {
 #pragma unroll
   for (int rho = K - 1; rho >= 0; --rho) {
     const int dist = 1 << (K - 1 - rho);
 #pragma unroll
     for (int j = 0; j < (1 << K); ++j) {
       if (j & dist) continue;
-      const uint32_t idx = (base << rho) + (uint32_t)(j >> (K - rho));
+      const typename Ar::TwT w = tw(rho, (uint32_t)(j >> (K - rho)));
       if (Ar::inv_red(rho, K))
-        A.template inv<true>(x[j], x[j + dist], idx);
+        A.template inv<true>(x[j], x[j + dist], w);
       else
-        A.template inv<false>(x[j], x[j + dist], idx);
+        A.template inv<false>(x[j], x[j + dist], w);
     }
   }
+}
+
+// With the twiddles read from the table where they are used.
+template <int K, int PS = -1, bool RED0 = true, bool UNI = false, class Ar>
+__device__ __forceinline__ void sub_fwd(const Ar& A, typename Ar::T* x, uint32_t base) {
+  sub_fwd_by<K, RED0>(A, x, [&](int rho, uint32_t g) {
+    return A.template twiddle<UNI>(PS < 0 ? (base << rho) + g
+                                          : base + ((1u << (PS + rho)) - (1u << PS)) + (g << (PS < 0 ? 0 : PS)));
+  });
+}
+template <int K, bool UNI = false, class Ar>
+__device__ __forceinline__ void sub_inv(const Ar& A, typename Ar::T* x, uint32_t base) {
+  sub_inv_by<K>(A, x, [&](int rho, uint32_t g) { return A.template twiddle<UNI>((base << rho) + g); });
+}
+
+// The 2^K - 1 twiddles of one subproblem, loaded ahead of use.
+template <int K, class Ar>
+__device__ __forceinline__ void load_sub_tw(const Ar& A, typename Ar::TwT (&w)[(1 << K) - 1], uint32_t base) {
+#pragma unroll
+  for (int rho = 0; rho < K; ++rho)
+#pragma unroll
+    for (int g = 0; g < (1 << rho); ++g) w[(1 << rho) - 1 + g] = A.template twiddle<false>((base << rho) + (uint32_t)g);
 }
 
 // Operands of HMUL or HROT folded into a fused KeySwitch (a == nullptr: a
@@ -406,8 +438,19 @@ struct BlockNtt {
     const int hi = p / L;
     return hi * (M >> s0) + lo + j * L;
   }
+  // Rounds whose butterfly groups are at least a wavefront wide: all lanes of a
+  // wave take the same twiddles, which come by scalar loads from the table (the
+  // first two of four rounds at blocks of 2^12 with E = 8: 14 of 28 twiddle reads
+  // of a thread, and the registers they took; (4, 2^16, 32), batch 8, 815 -> 809 us).
+  // With 4 elements a thread only the first round does: a scalar load is waited
+  // for together with all outstanding LDS accesses, which costs the latency variants
+  // more (one ciphertext of (2, 2^15, 10) from a graph 52.0 -> 54.1 us).
+  __device__ static constexpr bool uniform(int r) {
+    return r == 0 || (LOGE >= 3 && (M >> (round_s0(r) + round_k(r))) >= W);
+  }
   __device__ static __forceinline__ uint32_t base(int r, int tid, int u, uint32_t B0) {
     const int s0 = round_s0(r), k = round_k(r);
+    if (uniform(r)) tid = __builtin_amdgcn_readfirstlane(tid / W * W);
     const int p = tid + u * T;
     const int L = M >> (s0 + k);
     return (B0 << s0) + (uint32_t)(p / L);
@@ -421,18 +464,32 @@ struct BlockNtt {
   __device__ static __forceinline__ int fr_pos(int tid, int i) { return fr_base(tid) + fr_step(i); }
   __device__ static __forceinline__ int cl_pos(int tid, int i) { return cl_base(tid) + cl_step(i); }
 
-  template <int K, int PS = -1, class Ar>
-  __device__ static __forceinline__ void round_fwd(const Ar& A, typename Ar::T* x, int r, int tid, uint32_t B0) {
+  // The twiddles of a round that is not uniform (LOGE stages, one subproblem a
+  // thread), loaded before the exchange that precedes it. All rounds' together at
+  // the start of the transform, where they fit the registers, measured the same.
+  template <class Ar>
+  struct TwRegs {
+    typename Ar::TwT w[E - 1];
+  };
+  template <class Ar>
+  __device__ static __forceinline__ void load_round_tw(const Ar& A, TwRegs<Ar>& t, int r, int tid, uint32_t G0) {
+    load_sub_tw<LOGE>(A, t.w, base(r, tid, 0, G0));
+  }
+
+  // Round 0 of K1 stages is uniform: its groups are M >> K1 >= T elements wide.
+  template <class Ar>
+  __device__ static __forceinline__ void round0_fwd(const Ar& A, typename Ar::T* x, int tid, uint32_t G0) {
+    static_assert(uniform(0), "");
 #pragma unroll
-    for (int u = 0; u < (E >> K); ++u) sub_fwd<K, PS>(A, x + u * (1 << K), base(r, tid, u, B0));
+    for (int u = 0; u < (E >> K1); ++u) sub_fwd<K1, -1, true, true>(A, x + u * (1 << K1), base(0, tid, u, G0));
+  }
+  template <class Ar>
+  __device__ static __forceinline__ void round0_inv(const Ar& A, typename Ar::T* x, int tid, uint32_t G0) {
+#pragma unroll
+    for (int u = 0; u < (E >> K1); ++u) sub_inv<K1, true>(A, x + u * (1 << K1), base(0, tid, u, G0));
   }
   // First stage of the last round, where every thread has its own twiddles.
   static constexpr int LAST_S0 = LOGM - LOGE;
-  template <int K, class Ar>
-  __device__ static __forceinline__ void round_inv(const Ar& A, typename Ar::T* x, int r, int tid, uint32_t B0) {
-#pragma unroll
-    for (int u = 0; u < (E >> K); ++u) sub_inv<K>(A, x + u * (1 << K), base(r, tid, u, B0));
-  }
   __device__ static constexpr int round_l(int r) { return M >> (round_s0(r) + round_k(r)); }
   template <int K, class V>
   __device__ static __forceinline__ void to_lds(const V* x, V* lds, int r, int tid) {
@@ -475,23 +532,29 @@ struct BlockNtt {
     }
   }
 
-  // Forward: x enters in FR, leaves in CL. B0 = R + b. REUSE: a previous call
-  // read the LDS block, so a barrier precedes the first store. STAGED: the
-  // twiddles are a staged copy (B0 = 1) with the last round's stages stored
-  // group-major (sub_fwd with PS = LAST_S0).
+  // Forward: x enters in FR, leaves in CL. G0 = R + b. REUSE: a previous call
+  // read the LDS block, so a barrier precedes the first store. STAGED: A.tw is a
+  // staged copy of the block's twiddles with the last round's stages stored
+  // group-major (sub_fwd with PS = LAST_S0), read where they are used.
   template <bool STAGED = false, bool REUSE = false, class Ar>
-  __device__ static void fwd(const Ar& A, typename Ar::T* x, typename Ar::T* lds, int tid, uint32_t B0) {
-    round_fwd<K1>(A, x, 0, tid, B0);
+  __device__ static void fwd(const Ar& A, typename Ar::T* x, typename Ar::T* lds, int tid, uint32_t G0) {
+    round0_fwd(A, x, tid, G0);
     if (REUSE) __syncthreads();
     to_lds<K1>(x, lds, 0, tid);
 #pragma unroll
     for (int r = 1; r < NR; ++r) {
+      TwRegs<Ar> t;
+      if (!STAGED && !uniform(r)) load_round_tw(A, t, r, tid, G0);
       exchange_sync(wave_local(r - 1));
       from_lds<LOGE>(x, lds, r, tid);
-      if (STAGED && r == NR - 1)
-        round_fwd<LOGE, LAST_S0>(A, x, r, tid, B0);
+      if (uniform(r))
+        sub_fwd<LOGE, -1, true, true>(A, x, base(r, tid, 0, G0));
+      else if (STAGED && r == NR - 1)
+        sub_fwd<LOGE, LAST_S0>(A, x, base(r, tid, 0, 1u));
+      else if (STAGED)
+        sub_fwd<LOGE>(A, x, base(r, tid, 0, 1u));
       else
-        round_fwd<LOGE>(A, x, r, tid, B0);
+        sub_fwd_by<LOGE>(A, x, [&](int rho, uint32_t g) { return t.w[(1 << rho) - 1 + g]; });
       to_lds<LOGE>(x, lds, r, tid);
     }
     exchange_sync(true);
@@ -502,21 +565,26 @@ struct BlockNtt {
 
   // Inverse: x enters in CL, leaves in FR. REUSE as in fwd.
   template <bool REUSE = false, class Ar>
-  __device__ static void inv(const Ar& A, typename Ar::T* x, typename Ar::T* lds, int tid, uint32_t B0) {
+  __device__ static void inv(const Ar& A, typename Ar::T* x, typename Ar::T* lds, int tid, uint32_t G0) {
     if (REUSE) __syncthreads();
     typename Ar::T* c = lds + lds_pad(cl_base(tid));
 #pragma unroll
     for (int i = 0; i < E; ++i) c[pad_step(cl_step(i))] = x[i];
 #pragma unroll
     for (int r = NR - 1; r >= 1; --r) {
+      TwRegs<Ar> t;
+      if (!uniform(r)) load_round_tw(A, t, r, tid, G0);
       exchange_sync(r == NR - 1 || wave_local(r));  // the first read follows the CL stores
       from_lds<LOGE>(x, lds, r, tid);
-      round_inv<LOGE>(A, x, r, tid, B0);
+      if (uniform(r))
+        sub_inv<LOGE, true>(A, x, base(r, tid, 0, G0));
+      else
+        sub_inv_by<LOGE>(A, x, [&](int rho, uint32_t g) { return t.w[(1 << rho) - 1 + g]; });
       to_lds<LOGE>(x, lds, r, tid);
     }
     exchange_sync(wave_local(0));
     from_lds<K1>(x, lds, 0, tid);
-    round_inv<K1>(A, x, 0, tid, B0);
+    round0_inv(A, x, tid, G0);
   }
 };
 

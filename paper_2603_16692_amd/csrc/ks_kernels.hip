@@ -31,7 +31,8 @@ __device__ __forceinline__ size_t lane_col() { return (size_t)blockIdx.x * TC + 
 
 __device__ __forceinline__ ArF arf(const DevTables& tb, const LimbC& L, int limb, bool inverse) {
   const size_t N = (size_t)1 << tb.log_n;
-  return ArF{L.qd, L.qinv, (inverse ? tb.twi_d : tb.twf_d) + (size_t)limb * N};
+  const double* tw = (inverse ? tb.twi_d : tb.twf_d) + (size_t)limb * N;
+  return ArF{L.qd, L.qinv, tw, tw};
 }
 __device__ __forceinline__ ArI ari(const DevTables& tb, const LimbC& L, int limb, bool inverse) {
   const size_t N = (size_t)1 << tb.log_n;
@@ -763,22 +764,31 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
   uint64_t s0[B::E], s1[B::E], v[B::E];
 #pragma unroll
   for (int i = 0; i < B::E; ++i) s0[i] = s1[i] = 0;
+  // the next digit's input is loaded before a digit's transform (with K3 waiting for
+  // it after the products, (4, 2^16, 32), batch 8, was 828 us, now 809); the key
+  // blocks, L2 hits for all but one item, after it: one of them ahead as well
+  // takes the registers past 128
+  auto load_digit = [&](int j, uint64_t (&w)[B::E]) {
+    load_words<B>(ext1 + (((size_t)item * nslots + (slot_stride ? j : 0)) * nl + t) * N + boff, false, tid, w);
+  };
+  uint64_t nxt[B::E];
+  if (j0 < j1) load_digit(j0, nxt);
   for (int j = j0; j < j1; ++j) {
-    const int slot = slot_stride ? j : 0;
-    const uint64_t* src = ext1 + (((size_t)item * nslots + slot) * nl + t) * N + boff;
+    uint64_t w0[B::E], w1[B::E];
 #pragma unroll
-    for (int i = 0; i < B::E; ++i) v[i] = src[B::fr_pos(tid, i)];
+    for (int i = 0; i < B::E; ++i) v[i] = nxt[i];
+    if (j + 1 < j1) load_digit(j + 1, nxt);
     fwd_opaque<B>(A, v, lds, tid, B0);
-    const uint64_t* k0 = evk + key_row(tb, j, 0, t) * N + boff;
-    const uint64_t* k1 = evk + key_row(tb, j, 1, t) * N + boff;
+    load_words<B>(evk + key_row(tb, j, 0, t) * N + boff, true, tid, w0);
+    load_words<B>(evk + key_row(tb, j, 1, t) * N + boff, true, tid, w1);
+    // each product is below 1.5 * 2^60: folded every 8 digits, the sums stay below 2^64
 #pragma unroll
     for (int i = 0; i < B::E; ++i) {
-      const int x = B::cl_pos(tid, i);
-      // each product is below 1.5 * 2^60: folded every 8 digits, the sums stay below 2^64
-      const uint64_t vr = p_red(v[i], delta);
-      s0[i] += p_mul(vr, k0[x], delta);
-      s1[i] += p_mul(vr, k1[x], delta);
+      v[i] = p_red(v[i], delta);
+      s0[i] += p_mul(v[i], w0[i], delta);
     }
+#pragma unroll
+    for (int i = 0; i < B::E; ++i) s1[i] += p_mul(v[i], w1[i], delta);
     if (((j - j0) & 7) == 7) {
 #pragma unroll
       for (int i = 0; i < B::E; ++i) {
@@ -1006,8 +1016,8 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_blocks(DevTabl
 // table entry ((R + b) << s) + x - 2^s with s = floor(log2 x), the twiddle of
 // local stage s and group x - 2^s of block b. Stages s >= PS (the last round
 // of the forward pass) are stored group-major: group (p << (s - PS)) + g at
-// 2^s + (g << PS) + p. BlockNtt::fwd<true> with B0 = 1 and this table
-// computes what BlockNtt::fwd computes with B0 = R + b and the global table.
+// 2^s + (g << PS) + p. BlockNtt::fwd<true> with this table
+// computes what BlockNtt::fwd computes with the global table.
 // Thread tid moves entries tid + k T: past the first of them the stage is the
 // same for all threads. The loads and the stores are separate steps, so that all
 // loads of a thread are in flight together (one at a time, they were 5 us of
@@ -1077,8 +1087,9 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM <= 12) ? 4
   const LimbC L = tb.limb[i];
   const int nl = tb.nl, ell = tb.ell;
   const size_t boff = (size_t)b * B::M;
-  const ArF A{L.qd, L.qinv, TWL ? tw : tb.twf_d + (size_t)i * N};
-  const uint32_t B0 = TWL ? 1u : (uint32_t)(R + b);
+  const double* twg = tb.twf_d + (size_t)i * N;
+  const ArF A{L.qd, L.qinv, TWL ? tw : twg, twg};
+  const uint32_t G0 = (uint32_t)(R + b);
   const int own = i / tb.alpha;  // the digit whose limbs include i: its input is d, already in NTT form
   // Loads ahead of use (words as they are in memory, converted where they are
   // used): always the second t2 component and the first key component of a
@@ -1098,7 +1109,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM <= 12) ? 4
   uint64_t nxt[B::E];
   load_words<B>(t2 + (((size_t)item * 2 + 0) * ell + i) * N + boff, false, tid, nxt);
   double twr[B::E];
-  if constexpr (TWL) load_twiddles<B>(twr, tb.twf_d + (size_t)i * N, (uint32_t)(R + b), tid);
+  if constexpr (TWL) load_twiddles<B>(twr, twg, G0, tid);
 #pragma unroll
   for (int e = 0; e < B::E; ++e) cur[e] = raw2d(nxt[e]);
   load_words<B>(t2 + (((size_t)item * 2 + 1) * ell + i) * N + boff, false, tid, nxt);
@@ -1106,14 +1117,14 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM <= 12) ? 4
     store_twiddles<B>(twr, tw, tid);
     __syncthreads();
   }
-  fwd_opaque<B, TWL, false>(A, cur, ld, tid, B0);
+  fwd_opaque<B, TWL, false>(A, cur, ld, tid, G0);
 #pragma unroll
   for (int e = 0; e < B::E; ++e) {
     s0[e] = -f_red(cur[e], L.qd, L.qinv);
     cur[e] = raw2d(nxt[e]);
   }
   if (DEEP && j0 < j1) load_digit(j0, nxt);
-  fwd_opaque<B, TWL>(A, cur, ld, tid, B0);
+  fwd_opaque<B, TWL>(A, cur, ld, tid, G0);
 #pragma unroll
   for (int e = 0; e < B::E; ++e) s1[e] = -f_red(cur[e], L.qd, L.qinv);
   for (int j = j0; j < j1; ++j) {
@@ -1137,7 +1148,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM <= 12) ? 4
     } else {
 #pragma unroll
       for (int e = 0; e < B::E; ++e) cur[e] = raw2d(in[e]);
-      fwd_opaque<B, TWL>(A, cur, ld, tid, B0);
+      fwd_opaque<B, TWL>(A, cur, ld, tid, G0);
     }
     if constexpr (!DEEP) load_words<B>(k1, true, tid, w1);
 #pragma unroll
@@ -1223,7 +1234,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_keymult_pre(DevTables 
   }
 #pragma unroll
   for (int i = 0; i < B::E; ++i) s[i] = p_red(s[i], delta);
-  inv_opaque<B>(ari(tb, L, t, true), s, lds, tid, (uint32_t)R + b);
+  B::inv(ari(tb, L, t, true), s, lds, tid, (uint32_t)R + b);
   uint64_t* a = acc + (((size_t)item * 2 + c) * nl + t) * N + boff;
 #pragma unroll
   for (int i = 0; i < B::E; ++i) a[B::fr_pos(tid, i)] = s[i];
@@ -1258,7 +1269,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_pre(DevTables 
 #pragma unroll
     for (int e = 0; e < B::E; ++e) v[e] = raw2d(src[B::fr_pos(tid, e)]);
   }
-  fwd_opaque<B>(arf(tb, L, i, false), v, reinterpret_cast<double*>(lds), tid, (uint32_t)R + b);
+  B::fwd(arf(tb, L, i, false), v, reinterpret_cast<double*>(lds), tid, (uint32_t)R + b);
   double sum[B::E];
 #pragma unroll
   for (int e = 0; e < B::E; ++e) sum[e] = -f_red(v[e], L.qd, L.qinv);
