@@ -43,9 +43,9 @@ struct LimbC {
   double qd;           // q as a double (exact for the Q primes)
   double qinv;         // fl(1 / q)
   double ninv_d;       // balanced N^-1 mod q (Q primes)
-  // Recombination of the int8-MFMA base conversion (see k_modup_cols_mx):
-  double r32_d;        // balanced 2^32 mod q (Q primes)
-  uint64_t cadj;       // (-2^51 - 2^83) mod q (P primes)
+  // Recombination of the int8-MFMA base conversion (see mx_fold_q, mx_fold_p):
+  double qinv32, q32;  // 2^32 fl(1 / q), 2^-32 q (exact scalings; Q primes)
+  uint64_t cadj;       // (-2^51 - 2^83) mod q - 0x433 * 2^52 - 0x33 * 2^24 * (2^60 - q), mod 2^64 (P primes)
 };
 
 // Every table of one parameter set. Pointers are device addresses after

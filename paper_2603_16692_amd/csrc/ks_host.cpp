@@ -243,16 +243,15 @@ void build_tables(const HostParams& hp, std::vector<uint64_t>& blob, DevTables& 
     L.ninv = inv_prime(n % q, q);
     L.ninv_s = shoup(L.ninv, q);
     L.red_s = shoup(1, q);
-    {
-      uint64_t b = bal(((uint64_t)1 << 32) % q, q);
-      std::memcpy(&L.r32_d, &b, sizeof(b));
-    }
     // -(2^51 + 2^83) mod q
     const uint64_t c51 = ((uint64_t)1 << 51) % q;
     const uint64_t c83 = (uint64_t)(((u128)1 << 83) % q);
-    L.cadj = (2 * q - c51 - c83) % q;
+    // less the exponent bits that the device code leaves in the two words it adds
+    L.cadj = (2 * q - c51 - c83) % q - ((uint64_t)0x433 << 52) - ((uint64_t)0x33 << 24) * L.delta;
     L.qd = (double)q;
     L.qinv = 1.0 / (double)q;
+    L.qinv32 = L.qinv * 4294967296.0;
+    L.q32 = L.qd / 4294967296.0;
     {
       uint64_t b = bal(L.ninv, q);
       std::memcpy(&L.ninv_d, &b, sizeof(b));

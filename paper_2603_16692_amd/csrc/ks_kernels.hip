@@ -437,30 +437,34 @@ __device__ __forceinline__ mx_v16i mx_step(const ulonglong2& a, const ulonglong2
 
 // The target whose partial sums start at accumulator BASE (0 or 8), as
 // lo = C0 + 2^8 C1 + 2^16 C2 + 2^24 C3 and hi = C4 + ... + 2^24 C7, exact
-// doubles (each pair C + 2^8 C' below 2^30.1) below 2^46.1 in magnitude (the sum is lo + 2^32 hi).
-template <int BASE>
+// doubles (each pair C + 2^8 C' below 2^30.1) below 2^46.1 in magnitude (the sum is
+// lo + 2^32 hi). QG: a Q target, whose constants are below 2^50, so that C7 is 0.
+template <int BASE, bool QG>
 __device__ __forceinline__ void mx_halves(const mx_v16i& acc, double& lo, double& hi) {
   const int a0 = acc[BASE + 0] + acc[BASE + 1] * 256, a1 = acc[BASE + 2] + acc[BASE + 3] * 256;
-  const int b0 = acc[BASE + 4] + acc[BASE + 5] * 256, b1 = acc[BASE + 6] + acc[BASE + 7] * 256;
+  const int b0 = acc[BASE + 4] + acc[BASE + 5] * 256, b1 = QG ? acc[BASE + 6] : acc[BASE + 6] + acc[BASE + 7] * 256;
   lo = __fma_rn((double)a1, 65536.0, (double)a0);
   hi = __fma_rn((double)b1, 65536.0, (double)b0);
 }
 
-// lo + 2^32 hi mod q for a Q prime, |result| <= 0.6q: the product is within
-// q/2 + 0.1875 * 2^46.1, and |lo| < 2^46.1 < 0.07q.
-__device__ __forceinline__ double mx_fold_q(double lo, double hi, double q, double qinv, double r32) {
-  return lo + f_mul(hi, r32, q, qinv);
+// lo + 2^32 hi mod q for a Q prime, |result| <= 0.6q: k = rint(2^32 hi / q) (below
+// 2^30), and hi - k (q / 2^32) is a multiple of 2^-32 within (q/2 + 1) / 2^32, so
+// exact; |lo| < 2^46.1 < 0.07q. 4 instructions (a product with 2^32 mod q took 7;
+// (8, 2^17, 56), batch 2, 1126 us with it, 1108 without).
+__device__ __forceinline__ double mx_fold_q(double lo, double hi, double q32, double qinv32) {
+  return __fma_rn(__fma_rn(-__builtin_rint(hi * qinv32), q32, hi), 4294967296.0, lo);
 }
 
-// lo + 2^32 hi mod p for a P prime, below 2.1 * 2^60: with u = x + 2^51 >= 0 read
-// from the mantissa of x + 1.5 * 2^52, the value is
-// u_lo + 2^32 u_hi - 2^51 - 2^83, the bits of u_hi from 28 up fold at 2^60, and
-// cadj = (-2^51 - 2^83) mod p.
+// lo + 2^32 hi mod p for a P prime, below 2.1 * 2^60: with u = x + 2^51 >= 0 in the
+// mantissa of x + 1.5 * 2^52, the value is u_lo + 2^32 u_hi - 2^51 - 2^83, and the bits
+// of u_hi from 28 up fold at 2^60. The exponent bits stay in both words (0x433 in
+// the top 12 bits of u_lo's, 0x33 in the top 8 of the 32 bits taken from u_hi's): cadj
+// takes them out with the constant.
 __device__ __forceinline__ uint64_t mx_fold_p(double lo, double hi, const LimbC& L) {
-  const uint64_t ul = (uint64_t)__double_as_longlong(lo + 6755399441055744.0) & 0x000FFFFFFFFFFFFFull;
-  const uint64_t uh = (uint64_t)__double_as_longlong(hi + 6755399441055744.0) & 0x000FFFFFFFFFFFFFull;
-  return ul + ((uint64_t)((uint32_t)uh & 0x0FFFFFFFu) << 32) + (uint64_t)(uint32_t)(uh >> 28) * (uint32_t)L.delta +
-         L.cadj;
+  const uint64_t ul = (uint64_t)__double_as_longlong(lo + 6755399441055744.0);
+  const uint64_t uh = (uint64_t)__double_as_longlong(hi + 6755399441055744.0);
+  const uint32_t top = __builtin_amdgcn_alignbit((uint32_t)(uh >> 32), (uint32_t)uh, 28);
+  return ul + (uint64_t)top * (uint32_t)L.delta + ((uint64_t)((uint32_t)uh & 0x0FFFFFFFu) << 32) + L.cadj;
 }
 
 // Columns of a workgroup: 64 (two column halves of 32, one per wave parity), or
@@ -529,8 +533,7 @@ __device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2*
   const LimbC& LB = tb.limb[tc];
   using T = mx_val<QG>;
   T za[R], zb[R];
-  const double qa = LA.qd, qia = LA.qinv, r32a = LA.r32_d;
-  const double qb = LB.qd, qib = LB.qinv, r32b = LB.r32_d;
+  const double qa = LA.q32, qia = LA.qinv32, qb = LB.q32, qib = LB.qinv32;
   int yo = h * R * C + ycol;  // digit words of row r of step m: yp[yo + (2 m R + r) C]
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -539,16 +542,16 @@ __device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2*
     for (int m = 0; m < NM; ++m) acc = mx_step(cst[m], yp[yo + (2 * m * R + r) * C], acc);
     double lo, hi;
     if constexpr (PASS != 1) {
-      mx_halves<0>(acc, lo, hi);
+      mx_halves<0, QG>(acc, lo, hi);
       if constexpr (QG)
-        za[r] = mx_fold_q(lo, hi, qa, qia, r32a);
+        za[r] = mx_fold_q(lo, hi, qa, qia);
       else
         za[r] = mx_fold_p(lo, hi, LA);
     }
     if constexpr (PASS != 0) {
-      mx_halves<8>(acc, lo, hi);
+      mx_halves<8, QG>(acc, lo, hi);
       if constexpr (QG)
-        zb[r] = mx_fold_q(lo, hi, qb, qib, r32b);
+        zb[r] = mx_fold_q(lo, hi, qb, qib);
       else
         zb[r] = mx_fold_p(lo, hi, LB);
     }
