@@ -600,17 +600,20 @@ constexpr int mx_waves(int logr, int nm) { return logr <= 4 && mx_lds(logr, nm) 
 // Phase 2: with 64 columns wave w takes the column half w % 2 (lane l works on
 // column (w % 2) * 32 + l % 32 of the workgroup) and the target groups w/2,
 // w/2 + 4, ...; with 32 the groups w, w + 8, ...: per digit the Q targets outside
-// D_j in groups of four (in basis order), then the P targets.
+// D_j in groups of four (in basis order), then the P targets. With `parts` > 1 that
+// many workgroups share a tile's groups, each with its own phase 1 (mx_parts).
 template <int LOGR, int NM>
 __global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_modup_cols_mx(DevTables tb, const uint64_t* t1, uint64_t* ext1, int j0,
-                                                     int nslots, int slot_stride, int tgt0, int tgt1, int log_m) {
+                                                     int nslots, int slot_stride, int tgt0, int tgt1, int log_m,
+                                                     int parts) {
   constexpr int R = 1 << LOGR, C = mx_cols(LOGR, NM), SPW = TC / C;  // SPW: sources of a wave at a time
   extern __shared__ ulonglong2 yp[];
   const int M = 1 << log_m;
   const size_t N = (size_t)M * R;
   const int lane = threadIdx.x & (TC - 1), wv = threadIdx.x / TC;
   const int col = lane & (C - 1);
-  const size_t c = (size_t)blockIdx.x * C + col;
+  const int tile = blockIdx.x / parts, part = blockIdx.x % parts;
+  const size_t c = (size_t)tile * C + col;
   const bool live = c < (size_t)M;
   const int j = j0 + blockIdx.y;
   const int item = blockIdx.z;
@@ -641,13 +644,13 @@ __global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_modup_cols_mx(DevTab
   }
   __syncthreads();
   const int h = lane >> 5;
-  const size_t cc = (size_t)blockIdx.x * C + (C == 64 ? (wv & 1) * 32 : 0) + (lane & 31);
+  const size_t cc = (size_t)tile * C + (C == 64 ? (wv & 1) * 32 : 0) + (lane & 31);
   const bool clive = cc < (size_t)M;
   const int slot = slot_stride ? j : 0;
   uint64_t* e = ext1 + ((size_t)item * nslots + slot) * (size_t)nl * N;
   const int nq = ell - na, nqg = (nq + 3) >> 2, ng = nqg + ((k + 3) >> 2);
   const ulonglong2* cst_j = reinterpret_cast<const ulonglong2*>(tb.up_mx) + (size_t)j * tb.up_ng * nm * 64;
-  for (int g = wv / (C / 32); g < ng; g += CW / (C / 32)) {
+  for (int g = (wv / (C / 32)) * parts + part; g < ng; g += (CW / (C / 32)) * parts) {
     const bool qg = g < nqg;
     int tg[4];
     bool any = false;
@@ -906,14 +909,15 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_moddown_cols(DevTable
 // limbs that meet [tgt0, tgt1), shared out as in k_modup_cols_mx; output t2 raw.
 template <int LOGR, int NM>
 __global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_moddown_cols_mx(DevTables tb, const uint64_t* accp, uint64_t* t2, int tgt0,
-                                                       int tgt1, int log_m) {
+                                                       int tgt1, int log_m, int parts) {
   constexpr int R = 1 << LOGR, C = mx_cols(LOGR, NM), SPW = TC / C;
   extern __shared__ ulonglong2 yp[];
   const int M = 1 << log_m;
   const size_t N = (size_t)M * R;
   const int lane = threadIdx.x & (TC - 1), wv = threadIdx.x / TC;
   const int col = lane & (C - 1);
-  const size_t c = (size_t)blockIdx.x * C + col;
+  const int tile = blockIdx.x / parts, part = blockIdx.x % parts;
+  const size_t c = (size_t)tile * C + col;
   const bool live = c < (size_t)M;
   const int comp = blockIdx.y, item = blockIdx.z;
   const int ell = tb.ell, nl = tb.nl, k = tb.k;
@@ -939,11 +943,11 @@ __global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_moddown_cols_mx(DevT
   }
   __syncthreads();
   const int h = lane >> 5;
-  const size_t cc = (size_t)blockIdx.x * C + (C == 64 ? (wv & 1) * 32 : 0) + (lane & 31);
+  const size_t cc = (size_t)tile * C + (C == 64 ? (wv & 1) * 32 : 0) + (lane & 31);
   const bool clive = cc < (size_t)M;
   uint64_t* o = t2 + ((size_t)item * 2 + comp) * ell * N;
   const ulonglong2* cst = reinterpret_cast<const ulonglong2*>(tb.dn_mx);
-  for (int g = (tgt0 >> 2) + wv / (C / 32); 4 * g < tgt1; g += CW / (C / 32)) {
+  for (int g = (tgt0 >> 2) + (wv / (C / 32)) * parts + part; 4 * g < tgt1; g += (CW / (C / 32)) * parts) {
     const int ta = 4 * g + 2 * h, tb2 = ta + 1;
     const bool sa = clive && ta >= tgt0 && ta < tgt1;
     const bool sb = clive && tb2 >= tgt0 && tb2 < tgt1;
@@ -1766,13 +1770,28 @@ hipError_t by_nm(int nm, A... a) {
   else
     return nm == NM ? F<LOGR, NM>::run(a...) : by_nm<F, LOGR, NM + 1>(nm, a...);
 }
+// Workgroups that share the target groups of one column tile: doubled while a launch
+// has fewer than one workgroup for each CU and every wave still gets a group. One
+// ciphertext of (4, 2^16, 32) has 128 tiles in ModDown with two groups a wave: 28 us
+// there, 22 with two parts. With a workgroup on every CU the repeated phase 1 takes
+// what the shorter phase 2 gives (ModUp of the same call, 256 tiles: 37 and 38 us).
+inline int mx_parts(long tiles, int groups, int cols) {
+  int parts = 1;
+  while (tiles * parts < 256 && groups > (CW / (cols / 32)) * parts) parts *= 2;
+  return parts;
+}
+
 template <int LOGR, int NM>
 struct ModupColsMxN {
   static hipError_t run(const DevTables& tb, const uint64_t* t1, uint64_t* ext1, int j0, int nj, int nslots,
                         int slot_stride, int tgt0, int tgt1, int items, int log_m, hipStream_t s) {
     allow_lds<k_modup_cols_mx<LOGR, NM>>();
-    k_modup_cols_mx<LOGR, NM><<<col_grid(log_m, nj, items, mx_cols(LOGR, NM)), dim3(CT), mx_lds(LOGR, NM), s>>>(
-        tb, t1, ext1, j0, nslots, slot_stride, tgt0, tgt1, log_m);
+    dim3 g = col_grid(log_m, nj, items, mx_cols(LOGR, NM));
+    const int na = tb.alpha < tb.ell ? tb.alpha : tb.ell;
+    const int parts = mx_parts((long)g.x * g.y * g.z, (tb.ell - na + 3) / 4 + (tb.k + 3) / 4, mx_cols(LOGR, NM));
+    g.x *= parts;
+    k_modup_cols_mx<LOGR, NM><<<g, dim3(CT), mx_lds(LOGR, NM), s>>>(tb, t1, ext1, j0, nslots, slot_stride, tgt0, tgt1,
+                                                                    log_m, parts);
     return hipGetLastError();
   }
 };
@@ -1825,8 +1844,10 @@ struct ModdownColsMxN {
   static hipError_t run(const DevTables& tb, const uint64_t* accp, uint64_t* t2, int tgt0, int tgt1, int items,
                         int log_m, hipStream_t s) {
     allow_lds<k_moddown_cols_mx<LOGR, NM>>();
-    k_moddown_cols_mx<LOGR, NM><<<col_grid(log_m, 2, items, mx_cols(LOGR, NM)), dim3(CT), mx_lds(LOGR, NM), s>>>(
-        tb, accp, t2, tgt0, tgt1, log_m);
+    dim3 g = col_grid(log_m, 2, items, mx_cols(LOGR, NM));
+    const int parts = mx_parts((long)g.x * g.y * g.z, (tgt1 - tgt0 + 3) / 4, mx_cols(LOGR, NM));
+    g.x *= parts;
+    k_moddown_cols_mx<LOGR, NM><<<g, dim3(CT), mx_lds(LOGR, NM), s>>>(tb, accp, t2, tgt0, tgt1, log_m, parts);
     return hipGetLastError();
   }
 };
