@@ -469,10 +469,66 @@ __device__ __forceinline__ uint64_t mx_fold_p(double lo, double hi, const LimbC&
 
 // Columns of a workgroup: 64 (two column halves of 32, one per wave parity), or
 // 32 where the packed digits of 64 columns (2 KB nm R) would leave room for only
-// one workgroup of 8 waves on a CU. With 32 rows the registers do that anyway, and
+// one workgroup of 8 waves on a CU. With 32 rows the registers do that anyway (built
+// for two workgroups they spill: ModUp of (4, 2^16, 32), batch 8, 229 -> 298 us), and
 // it is 64 columns as long as they fit.
 constexpr int mx_cols(int logr, int nm) { return (nm << logr) <= (logr == 5 ? 64 : 40) ? 64 : 32; }
-constexpr int mx_lds(int logr, int nm) { return (nm << logr) * mx_cols(logr, nm) * 32; }
+// From 16 rows on, the first R twiddles of a group's four targets go through the
+// wave's own part of the LDS: one or two loads a lane, in flight with the constants
+// and stored when the rows are done. Read where each stage uses them, from two
+// addresses a wave, they took the registers that the rows need and a latency a
+// stage (ModUp of (4, 2^16, 32), batch 8, 181 -> 168 us, with the registers no longer
+// spilling); with 8 rows (7 twiddles) the detour costs 2% of (2, 2^15, 10), batch 32.
+constexpr bool mx_twl(int logr) { return logr >= 4; }
+constexpr int mx_nt(int logr) { return mx_twl(logr) ? (4 << logr) / 64 : 1; }
+// LDS: the packed digits, and that part for each wave (16 bytes each, for P targets).
+constexpr int mx_lds(int logr, int nm) {
+  return (nm << logr) * mx_cols(logr, nm) * 32 + (mx_twl(logr) ? CW * 4 * (16 << logr) : 0);
+}
+
+// The other half of the lanes' registers: a keeps its lower 32 lanes and takes b's
+// lower into its upper ones, b keeps its upper and takes a's upper into its lower.
+__device__ __forceinline__ void swap32(uint64_t& a, uint64_t& b) {
+  typedef unsigned v2 __attribute__((ext_vector_type(2)));
+  const v2 lo = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+  const v2 hi = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+  a = ((uint64_t)hi.x << 32) | lo.x;
+  b = ((uint64_t)hi.y << 32) | lo.y;
+}
+__device__ __forceinline__ void swap32(double& a, double& b) {
+  uint64_t x = d2raw(a), y = d2raw(b);
+  swap32(x, y);
+  a = raw2d(x);
+  b = raw2d(y);
+}
+
+// Inverse column pass of one source by one wave. With 64 columns a lane holds the R
+// rows of its column. With 32 lane half h loads rows h R/2 .. (v[i] is row i + h R/2),
+// and after the stages within a half the halves exchange R/4 registers, so that the
+// last stage's pairs (row r, row r + R/2) meet in one lane: v[i] is then row
+// i + h R/4 and v[i + R/4] row R/2 + i + h R/4, i < R/4 (mx_row).
+template <int LOGR, int C>
+constexpr int mx_rows() { return C == 64 ? 1 << LOGR : (1 << LOGR) / 2; }
+template <int LOGR, int C>
+__device__ __forceinline__ int mx_row(int i, int h) {
+  constexpr int R = 1 << LOGR;
+  return C == 64 ? i : (i < R / 4 ? i + h * (R / 4) : R / 2 + (i - R / 4) + h * (R / 4));
+}
+template <int LOGR, int C, class Ar>
+__device__ __forceinline__ void mx_inv(const Ar& A, typename Ar::T (&v)[mx_rows<LOGR, C>()], int h) {
+  if constexpr (C == 64) {
+    sub_inv<LOGR>(A, v, 1u);
+  } else {
+    constexpr int Q = (1 << LOGR) / 4;
+    sub_inv<LOGR - 1>(A, v, 2u + (uint32_t)h);
+    const typename Ar::TwT w = A.template twiddle<false>(1u);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      swap32(v[i], v[i + Q]);
+      A.template inv<true>(v[i], v[i + Q], w);
+    }
+  }
+}
 
 // Phase 2 of the MFMA column kernels for one target group. A lane in half h
 // holds the partial sums of targets 2h and 2h + 1 of the group; each is
@@ -486,11 +542,13 @@ constexpr int mx_lds(int logr, int nm) { return (nm << logr) * mx_cols(logr, nm)
 // so the stores are non-temporal (measured: 5% off the ModUp column kernel).
 template <bool QG>
 using mx_val = typename std::conditional<QG, double, uint64_t>::type;
+template <bool QG>
+using mx_tw = typename std::conditional<QG, double, ulonglong2>::type;
 
 // CONV: the conversion alone (ks_bconv): no transform, canonical words.
 template <int LOGR, bool QG, bool CONV>
-__device__ __forceinline__ void mx_finish(const DevTables& tb, const LimbC& L, int t, mx_val<QG> (&z)[1 << LOGR],
-                                          bool st, uint64_t* o, size_t cc, int M) {
+__device__ __forceinline__ void mx_finish(const LimbC& L, const mx_tw<QG>* tw, mx_val<QG> (&z)[1 << LOGR], bool st,
+                                          uint64_t* o, size_t cc, int M) {
   constexpr int R = 1 << LOGR;
   if constexpr (CONV) {
     if (st) {
@@ -505,9 +563,9 @@ __device__ __forceinline__ void mx_finish(const DevTables& tb, const LimbC& L, i
     return;
   }
   if constexpr (QG)
-    sub_fwd<LOGR, -1, false>(arf(tb, L, t, false), z, 1u);
+    sub_fwd<LOGR, -1, false>(ArF{L.qd, L.qinv, tw, tw}, z, 1u);
   else
-    sub_fwd<LOGR, -1, false>(ari(tb, L, t, false), z, 1u);
+    sub_fwd<LOGR, -1, false>(ArI{L.q, L.nq, (uint32_t)L.delta, reinterpret_cast<const uint64_t*>(tw)}, z, 1u);
   if (st) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -522,8 +580,8 @@ __device__ __forceinline__ void mx_finish(const DevTables& tb, const LimbC& L, i
 }
 
 template <int LOGR, bool QG, int NM, int PASS, bool CONV>
-__device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2* yp, const ulonglong2 (&cst)[NM],
-                                          int ta0, int ta1, int tb0, int tb1, bool sa, bool sb, uint64_t* oa,
+__device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2* yp, mx_tw<QG>* tw,
+                                          const mx_tw<QG> (&wl)[mx_nt(LOGR)], const ulonglong2 (&cst)[NM], int ta0, int ta1, int tb0, int tb1, bool sa, bool sb, uint64_t* oa,
                                           uint64_t* ob, size_t cc, int M) {
   constexpr int R = 1 << LOGR, C = mx_cols(LOGR, NM);
   const int lane = threadIdx.x & (TC - 1), h = lane >> 5;
@@ -565,26 +623,64 @@ __device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2*
     else
       asm volatile("" : "+v"(za[r]), "+v"(zb[r]), "+v"(yo));
   }
-  if constexpr (PASS != 1) mx_finish<LOGR, QG, CONV>(tb, LA, ta, za, sa, oa, cc, M);
-  if constexpr (PASS != 0) mx_finish<LOGR, QG, CONV>(tb, LB, tc, zb, sb, ob, cc, M);
+  const mx_tw<QG>*wa, *wb;
+  if constexpr (mx_twl(LOGR)) {
+    if constexpr (!CONV && PASS != 1) {
+#pragma unroll
+      for (int n = 0; n < mx_nt(LOGR); ++n) tw[lane + 64 * n] = wl[n];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    wa = tw + (size_t)(2 * h) * R;
+    wb = tw + (size_t)(2 * h + 1) * R;
+  } else {
+    const mx_tw<QG>* tab;
+    if constexpr (QG)
+      tab = tb.twf_d;
+    else
+      tab = reinterpret_cast<const ulonglong2*>(tb.twf);
+    wa = tab + ((size_t)ta << tb.log_n);
+    wb = tab + ((size_t)tc << tb.log_n);
+  }
+  if constexpr (PASS != 1) mx_finish<LOGR, QG, CONV>(LA, wa, za, sa, oa, cc, M);
+  if constexpr (PASS != 0) mx_finish<LOGR, QG, CONV>(LB, wb, zb, sb, ob, cc, M);
 }
 
 // lt[4]: the group's four limbs (padding slots replaced by a stand-in limb,
 // wave-uniform); lane half h finishes targets lt[2h] (stored if sa, at oa)
 // and lt[2h + 1] (if sb, at ob).
-template <int LOGR, bool QG, int NM, bool CONV = false>
+template <int LOGR, bool QG, int NM, bool CONV = false, int C = mx_cols(LOGR, NM)>
 __device__ __forceinline__ void mx_group(const DevTables& tb, const ulonglong2* yp, const ulonglong2* cst_g,
                                          const int (&lt)[4], bool sa, bool sb, uint64_t* oa, uint64_t* ob,
                                          size_t cc, int M) {
   const int lane = threadIdx.x & (TC - 1);
+  constexpr int R = 1 << LOGR;
+  using TW = mx_tw<QG>;
+  TW* tw = reinterpret_cast<TW*>(const_cast<ulonglong2*>(yp) + NM * R * C * 2) +
+           (size_t)(threadIdx.x / TC) * (4 * R) * (QG ? 2 : 1);
+  TW wl[mx_nt(LOGR)];
+  if constexpr (!CONV && mx_twl(LOGR)) {
+    const int l0 = lt[0], l1 = lt[1], l2 = lt[2], l3 = lt[3];
+#pragma unroll
+    for (int n = 0; n < mx_nt(LOGR); ++n) {
+      const int e = lane + 64 * n, slot = e >> LOGR;
+      const int t = slot == 0 ? l0 : slot == 1 ? l1 : slot == 2 ? l2 : l3;
+      const size_t x = ((size_t)t << tb.log_n) + (size_t)(e & (R - 1));
+      if constexpr (QG)
+        wl[n] = tb.twf_d[x];
+      else
+        wl[n] = reinterpret_cast<const ulonglong2*>(tb.twf)[x];
+    }
+  }
   ulonglong2 cst[NM];
 #pragma unroll
   for (int m = 0; m < NM; ++m) cst[m] = cst_g[m * 64 + lane];
   if constexpr (LOGR <= 3) {
-    mx_target<LOGR, QG, NM, 2, CONV>(tb, yp, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
+    mx_target<LOGR, QG, NM, 2, CONV>(tb, yp, tw, wl, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
   } else {
-    mx_target<LOGR, QG, NM, 0, CONV>(tb, yp, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
-    mx_target<LOGR, QG, NM, 1, CONV>(tb, yp, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
+    mx_target<LOGR, QG, NM, 0, CONV>(tb, yp, tw, wl, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
+    mx_target<LOGR, QG, NM, 1, CONV>(tb, yp, tw, wl, cst, lt[0], lt[2], lt[1], lt[3], sa, sb, oa, ob, cc, M);
   }
 }
 
@@ -595,8 +691,8 @@ constexpr int mx_waves(int logr, int nm) { return logr <= 4 && mx_lds(logr, nm) 
 // ModUp columns with the int8-MFMA BConv: same arguments and output as
 // k_modup_cols. Phase 1: inverse column pass and pre-scale as in k_modup_cols,
 // canonical y packed into LDS as [pair][R][columns] x 16 bytes (pair p = sources
-// 2p, 2p + 1; zero past the digit's sources and for columns past M); with 64
-// columns a wave takes one source at a time, with 32 one in each lane half.
+// 2p, 2p + 1; zero past the digit's sources and for columns past M); a wave takes
+// one source at a time (mx_inv).
 // Phase 2: with 64 columns wave w takes the column half w % 2 (lane l works on
 // column (w % 2) * 32 + l % 32 of the workgroup) and the target groups w/2,
 // w/2 + 4, ...; with 32 the groups w, w + 8, ...: per digit the Q targets outside
@@ -606,7 +702,7 @@ template <int LOGR, int NM>
 __global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_modup_cols_mx(DevTables tb, const uint64_t* t1, uint64_t* ext1, int j0,
                                                      int nslots, int slot_stride, int tgt0, int tgt1, int log_m,
                                                      int parts) {
-  constexpr int R = 1 << LOGR, C = mx_cols(LOGR, NM), SPW = TC / C;  // SPW: sources of a wave at a time
+  constexpr int R = 1 << LOGR, C = mx_cols(LOGR, NM), RL = mx_rows<LOGR, C>();  // RL: rows of a lane in phase 1
   extern __shared__ ulonglong2 yp[];
   const int M = 1 << log_m;
   const size_t N = (size_t)M * R;
@@ -622,25 +718,26 @@ __global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_modup_cols_mx(DevTab
   const int na = min(lo + tb.alpha, ell) - lo;
   constexpr int nm = NM;  // = tb.up_nm
   uint64_t* yw = reinterpret_cast<uint64_t*>(yp);
-  for (int s = wv * SPW + lane / C; s < 4 * nm; s += CW * SPW) {
-    uint64_t y[R];
-    if (live && s < na) {
+  const int ph = C == 64 ? 0 : lane >> 5;  // row half of phase 1
+  for (int s = wv; s < 4 * nm; s += CW) {
+    uint64_t* yr = yw + (size_t)(s >> 1) * R * C * 2 + 2 * col + (s & 1);  // row r at yr[2 r C]
+    if (s < na && (C == 32 || live)) {  // with 32 columns uniform: those past M read the last one's words
       const int i = lo + s;
       const LimbC L = tb.limb[i];
-      const uint64_t* a = t1 + ((size_t)item * ell + i) * N;
-      double v[R];
+      const uint64_t* a = t1 + ((size_t)item * ell + i) * N + (C == 64 || live ? c : M - 1) + (size_t)(ph * RL) * M;
+      double v[RL];
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[r] = raw2d(a[c + (size_t)r * M]);
-      sub_inv<LOGR>(arf(tb, L, i, true), v, 1u);
+      for (int r = 0; r < RL; ++r) v[r] = raw2d(a[(size_t)r * M]);
+      mx_inv<LOGR, C>(arf(tb, L, i, true), v, ph);
       const double w = tb.up_pre_d[i];
 #pragma unroll
-      for (int r = 0; r < R; ++r) y[r] = mx_pack_q(f_canon_d(f_mul(v[r], w, L.qd, L.qinv), L.qd, L.qinv));
+      for (int r = 0; r < RL; ++r)
+        yr[2 * C * mx_row<LOGR, C>(r, ph)] =
+            C == 64 || live ? mx_pack_q(f_canon_d(f_mul(v[r], w, L.qd, L.qinv), L.qd, L.qinv)) : 0;
     } else {
 #pragma unroll
-      for (int r = 0; r < R; ++r) y[r] = 0;
+      for (int r = 0; r < RL; ++r) yr[2 * C * mx_row<LOGR, C>(r, ph)] = 0;
     }
-#pragma unroll
-    for (int r = 0; r < R; ++r) yw[((size_t)((s >> 1) * R + r) * C + col) * 2 + (s & 1)] = y[r];
   }
   __syncthreads();
   const int h = lane >> 5;
@@ -910,7 +1007,7 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_moddown_cols(DevTable
 template <int LOGR, int NM>
 __global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_moddown_cols_mx(DevTables tb, const uint64_t* accp, uint64_t* t2, int tgt0,
                                                        int tgt1, int log_m, int parts) {
-  constexpr int R = 1 << LOGR, C = mx_cols(LOGR, NM), SPW = TC / C;
+  constexpr int R = 1 << LOGR, C = mx_cols(LOGR, NM), RL = mx_rows<LOGR, C>();
   extern __shared__ ulonglong2 yp[];
   const int M = 1 << log_m;
   const size_t N = (size_t)M * R;
@@ -923,23 +1020,26 @@ __global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_moddown_cols_mx(DevT
   const int ell = tb.ell, nl = tb.nl, k = tb.k;
   constexpr int nm = NM;  // = tb.dn_nm
   uint64_t* yw = reinterpret_cast<uint64_t*>(yp);
-  for (int m = wv * SPW + lane / C; m < 4 * nm; m += CW * SPW) {
-    uint64_t y[R];
-    if (live && m < k) {
+  const int ph = C == 64 ? 0 : lane >> 5;
+  for (int m = wv; m < 4 * nm; m += CW) {
+    uint64_t* yr = yw + (size_t)(m >> 1) * R * C * 2 + 2 * col + (m & 1);
+    if (m < k && (C == 32 || live)) {
       const LimbC L = tb.limb[ell + m];
-      const uint64_t* a = accp + (((size_t)item * 2 + comp) * nl + ell + m) * N;
+      const uint64_t* a =
+          accp + (((size_t)item * 2 + comp) * nl + ell + m) * N + (C == 64 || live ? c : M - 1) + (size_t)(ph * RL) * M;
+      uint64_t v[RL];
 #pragma unroll
-      for (int r = 0; r < R; ++r) y[r] = a[c + (size_t)r * M];
-      sub_inv<LOGR>(ari(tb, L, ell + m, true), y, 1u);
+      for (int r = 0; r < RL; ++r) v[r] = a[(size_t)r * M];
+      mx_inv<LOGR, C>(ari(tb, L, ell + m, true), v, ph);
       const uint64_t w = tb.dn_pre[2 * m], ws = tb.dn_pre[2 * m + 1];
 #pragma unroll
-      for (int r = 0; r < R; ++r) y[r] = mx_pack(p_canon(mul_shoup_lazy(y[r], w, ws, L.nq), L.q, L.delta));
+      for (int r = 0; r < RL; ++r)
+        yr[2 * C * mx_row<LOGR, C>(r, ph)] =
+            C == 64 || live ? mx_pack(p_canon(mul_shoup_lazy(v[r], w, ws, L.nq), L.q, L.delta)) : 0;
     } else {
 #pragma unroll
-      for (int r = 0; r < R; ++r) y[r] = 0;
+      for (int r = 0; r < RL; ++r) yr[2 * C * mx_row<LOGR, C>(r, ph)] = 0;
     }
-#pragma unroll
-    for (int r = 0; r < R; ++r) yw[((size_t)((m >> 1) * R + r) * C + col) * 2 + (m & 1)] = y[r];
   }
   __syncthreads();
   const int h = lane >> 5;
