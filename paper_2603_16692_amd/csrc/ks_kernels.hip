@@ -1737,10 +1737,15 @@ hipError_t by_logr(int log_r, A... a) {
   }
 }
 
-// Elements per thread of the plain block passes: 16 from blocks of 2^12 on,
-// 8 below (twice the threads per block, which small transforms need to fill
-// the chip: -22% on (2, 2^13, 6) with one ciphertext).
-constexpr int loge_for(int logm) { return logm >= 12 ? 4 : (logm >= 6 ? 3 : (logm >= 4 ? 2 : 1)); }
+// Elements per thread of the plain block passes: 8 up to blocks of 2^12 (twice the
+// threads per block that 16 give, which small transforms need to fill the chip: -22%
+// on (2, 2^13, 6) with one ciphertext; at 2^12, -2% on modup + keymult + moddown and
+// on HMUL of (4, 2^16, 32)) and 16 beyond. The plain inverse pass and the passes of
+// KS_PLAN_HOIST_FWD take 16 at 2^12 too: one LDS exchange less, 2% of
+// (2, 2^15, 10), batch 32.
+constexpr int loge_for(int logm, bool lean) {
+  return logm >= (lean ? 12 : 13) ? 4 : (logm >= 6 ? 3 : (logm >= 4 ? 2 : 1));
+}
 
 // Latency variant of a block pass: 4 elements per thread (8 at blocks of
 // 2^13), so that a block of 2^11 to 2^13 coefficients runs on 512 to 1024
@@ -1758,12 +1763,13 @@ inline bool use_lat(int logm, int loge, long wgs) {
   return logm >= 8 && logm <= 13 && loge_lat(logm) < loge && wgs * (1L << (logm - loge)) < (1L << 18);
 }
 
-template <template <int, int> class F, typename... A>
+template <template <int, int> class F, bool LEAN = false, typename... A>
 hipError_t by_logm(int log_m, long wgs, A... a) {
   switch (log_m) {
 #define KS_CASE(m) \
-  case m:          \
-    return use_lat(m, loge_for(m), wgs) ? F<m, loge_lat(m)>::run(a...) : F<m, loge_for(m)>::run(a...);
+  case m:                                                                             \
+    return use_lat(m, loge_for(m, LEAN), wgs) ? F<m, loge_lat(m)>::run(a...) \
+                                                   : F<m, loge_for(m, LEAN)>::run(a...);
     KS_CASE(3) KS_CASE(4) KS_CASE(5) KS_CASE(6) KS_CASE(7) KS_CASE(8) KS_CASE(9) KS_CASE(10) KS_CASE(11)
     KS_CASE(12) KS_CASE(13) KS_CASE(14)
 #undef KS_CASE
@@ -2088,7 +2094,7 @@ hipError_t launch_ntt(const DevTables& tb, int log_r, uint64_t* x, int first, in
 
 hipError_t launch_intt(const DevTables& tb, int log_r, uint64_t* x, int first, int nlimbs, int items, hipStream_t s) {
   const int log_m = tb.log_n - log_r;
-  hipError_t e = by_logm<BlocksInv>(log_m, (long)(nlimbs << log_r) * items, tb, (const uint64_t*)x, x, first, nlimbs,
+  hipError_t e = by_logm<BlocksInv, true>(log_m, (long)(nlimbs << log_r) * items, tb, (const uint64_t*)x, x, first, nlimbs,
                                     items, log_r == 0 ? 1 : 0, s);
   if (e != hipSuccess || log_r == 0) return e;
   return by_logr<ColsInv>(log_r, tb, x, first, nlimbs, items, log_m, s);
@@ -2096,7 +2102,7 @@ hipError_t launch_intt(const DevTables& tb, int log_r, uint64_t* x, int first, i
 
 hipError_t launch_intt_blocks(const DevTables& tb, int log_r, const uint64_t* src, uint64_t* dst, int nlimbs,
                               int items, hipStream_t s) {
-  return by_logm<BlocksInv>(tb.log_n - log_r, (long)(nlimbs << log_r) * items, tb, src, dst, 0, nlimbs, items, 0, s);
+  return by_logm<BlocksInv, true>(tb.log_n - log_r, (long)(nlimbs << log_r) * items, tb, src, dst, 0, nlimbs, items, 0, s);
 }
 
 hipError_t launch_eval_blocks(const DevTables& tb, int log_r, EvalIn ev, uint64_t* d2, uint64_t* t1, int items,
@@ -2116,7 +2122,12 @@ hipError_t launch_keymult_blocks(const DevTables& tb, int log_r, const uint64_t*
                                  const uint64_t* evk, uint64_t* acc, int j0, int j1, int nslots, int slot_stride,
                                  int tgt0, int tgt1, int items, int accumulate, int finalize, int q_part,
                                  hipStream_t s) {
-  return by_logm_k3<KeymultBlocks>(tb.log_n - log_r, (long)((tgt1 - tgt0) << log_r) * items, tb, d, ext1, evk, acc,
+  // Without q_part only the P limbs are launched, and the latency variant pays only
+  // where they leave CUs without a workgroup (128 of them, one ciphertext of
+  // (4, 2^16, 32): 162 -> 157 us the call; with 384, level 13 of it, batch 3, 158 -> 163).
+  const long wgs = q_part ? (long)((tgt1 - tgt0) << log_r) * items
+                          : 2 * ((long)((tgt1 - (tgt0 > tb.ell ? tgt0 : tb.ell)) << log_r) * items);
+  return by_logm_k3<KeymultBlocks>(tb.log_n - log_r, wgs, tb, d, ext1, evk, acc,
                                    j0, j1, nslots, slot_stride, tgt0, tgt1, items, accumulate, finalize, q_part, s);
 }
 
@@ -2147,19 +2158,19 @@ hipError_t launch_ext_blocks(const DevTables& tb, int log_r, uint64_t* ext, int 
 
 hipError_t launch_keymult_pre(const DevTables& tb, int log_r, const uint64_t* ext1, const uint64_t* evk,
                               uint64_t* acc, int items, hipStream_t s) {
-  return by_logm<KeymultPre>(tb.log_n - log_r, (long)(tb.k << log_r) * items * 2, tb, ext1, evk, acc, items, s);
+  return by_logm<KeymultPre, true>(tb.log_n - log_r, (long)(tb.k << log_r) * items * 2, tb, ext1, evk, acc, items, s);
 }
 
 hipError_t launch_moddown_pre(const DevTables& tb, int log_r, const uint64_t* d, const uint64_t* ext1,
                               const uint64_t* evk, const uint64_t* t2, uint64_t* out, int items, EvalIn ev,
                               hipStream_t s) {
-  return by_logm<ModdownPre>(tb.log_n - log_r, (long)(tb.ell << log_r) * items * 2, tb, d, ext1, evk, t2, out, items,
+  return by_logm<ModdownPre, true>(tb.log_n - log_r, (long)(tb.ell << log_r) * items * 2, tb, d, ext1, evk, t2, out, items,
                              ev, s);
 }
 
 hipError_t launch_pblocks_inv(const DevTables& tb, int log_r, const uint64_t* acc, uint64_t* accp, int items,
                               hipStream_t s) {
-  return by_logm<PBlocksInv>(tb.log_n - log_r, (long)(tb.k << log_r) * items * 2, tb, acc, accp, items, s);
+  return by_logm<PBlocksInv, true>(tb.log_n - log_r, (long)(tb.k << log_r) * items * 2, tb, acc, accp, items, s);
 }
 
 hipError_t launch_copy_digits(const DevTables& tb, const uint64_t* d, uint64_t* ext, int items, hipStream_t s) {
