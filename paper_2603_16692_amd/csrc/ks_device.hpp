@@ -158,9 +158,17 @@ __device__ __forceinline__ double f_red(double x, double q, double qinv) {
   return __fma_rn(-__builtin_rint(x * qinv), q, x);
 }
 
-// Exact conversion of an integer 0 <= v < 2^52.
+// Exact conversion of an integer 0 <= v < 2^53: its bits are those of the subnormal
+// (or, from 2^52 on, smallest normal) double v 2^-1074. One instruction; an or and
+// an addition through 2^52 are 1.6 (a 32-bit logic operation issues in 2.4 cycles a
+// wavefront, any other in 4.2).
 __device__ __forceinline__ double u2d(uint64_t v) {
-  return __longlong_as_double((long long)(v | 0x4330000000000000ull)) - 4503599627370496.0;
+  return __builtin_ldexp(__longlong_as_double((long long)v), 1074);
+}
+
+// Exact conversion of an integer-valued double in [0, 2^53).
+__device__ __forceinline__ uint64_t d2u(double v) {
+  return (uint64_t)__double_as_longlong(__builtin_ldexp(v, -1074));
 }
 
 // Canonical residue in [0, q) of an integer-valued |x| <= 1.9q, as a double.
@@ -174,11 +182,6 @@ __device__ __forceinline__ double f_canon_d(double x, double q, double qinv) {
 // The same for an integer-valued |x| < 2^53.
 __device__ __forceinline__ double f_canon_wide_d(double x, double q, double qinv) {
   return f_canon_d(f_red(x, q, qinv), q, qinv);
-}
-
-// Exact conversion of an integer-valued double in [0, 2^52).
-__device__ __forceinline__ uint64_t d2u(double v) {
-  return (uint64_t)__double_as_longlong(v + 4503599627370496.0) & 0x000FFFFFFFFFFFFFull;
 }
 
 // Canonical residue as uint64, of |x| <= 1.9q and of |x| < 2^53.
