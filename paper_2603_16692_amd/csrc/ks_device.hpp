@@ -538,9 +538,15 @@ struct BlockNtt {
   // Forward: x enters in FR, leaves in CL. G0 = R + b. REUSE: a previous call
   // read the LDS block, so a barrier precedes the first store. STAGED: A.tw is a
   // staged copy of the block's twiddles with the last round's stages stored
-  // group-major (sub_fwd with PS = LAST_S0), read where they are used.
-  template <bool STAGED = false, bool REUSE = false, class Ar>
-  __device__ static void fwd(const Ar& A, typename Ar::T* x, typename Ar::T* lds, int tid, uint32_t G0) {
+  // group-major (sub_fwd with PS = LAST_S0), read where they are used. `between(r)`
+  // runs before the exchange that precedes round r: loads that a kernel needs after
+  // the transform, spread over it.
+  struct Nothing {
+    __device__ __forceinline__ void operator()(int) const {}
+  };
+  template <bool STAGED = false, bool REUSE = false, class Ar, class H = Nothing>
+  __device__ static __forceinline__ void fwd(const Ar& A, typename Ar::T* x, typename Ar::T* lds, int tid, uint32_t G0,
+                                             H between = H()) {
     round0_fwd(A, x, tid, G0);
     if (REUSE) __syncthreads();
     to_lds<K1>(x, lds, 0, tid);
@@ -548,6 +554,7 @@ struct BlockNtt {
     for (int r = 1; r < NR; ++r) {
       TwRegs<Ar> t;
       if (!STAGED && !uniform(r)) load_round_tw(A, t, r, tid, G0);
+      between(r);
       exchange_sync(wave_local(r - 1));
       from_lds<LOGE>(x, lds, r, tid);
       if (uniform(r))

@@ -63,12 +63,12 @@ inline unsigned xcd_grid(int ntiles, int items) { return (unsigned)(((ntiles + 7
 // runs several transforms would otherwise keep every LDS and twiddle address
 // of all rounds live from the first transform to the last, which costs more
 // registers than recomputing them.
-template <class B, bool STAGED = false, bool REUSE = true, class Ar>
-__device__ __forceinline__ void fwd_opaque(const Ar& A, typename Ar::T* v, typename Ar::T* ld, int tid,
-                                           uint32_t B0) {
+template <class B, bool STAGED = false, bool REUSE = true, class Ar, class H = typename B::Nothing>
+__device__ __forceinline__ void fwd_opaque(const Ar& A, typename Ar::T* v, typename Ar::T* ld, int tid, uint32_t B0,
+                                           H between = H()) {
   int t = tid;
   asm volatile("" : "+v"(t));
-  B::template fwd<STAGED, REUSE>(A, v, ld, t, B0);
+  B::template fwd<STAGED, REUSE>(A, v, ld, t, B0, between);
 }
 template <class B, bool REUSE = true, class Ar>
 __device__ __forceinline__ void inv_opaque(const Ar& A, typename Ar::T* v, typename Ar::T* ld, int tid,
@@ -1242,20 +1242,32 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM <= 12) ? 4
 #pragma unroll
       for (int e = 0; e < B::E; ++e) in[e] = nxt[e];
     }
-    load_words<B>(k0, true, tid, w0);
+    // The next input goes out before the transform, the key blocks before its last two
+    // exchanges: all 24 loads of a thread at once hold a wave at their issue (the key
+    // blocks, L2 hits, were 51 of the kernel's 352 us at (4, 2^16, 32), batch 8). The
+    // call: 762 -> 754 us; (8, 2^17, 56), batch 2, 1063 -> 1046.
     if constexpr (DEEP) {
-      load_words<B>(k1, true, tid, w1);
       if (j + 1 < j1) load_digit(j + 1, nxt);
     } else {
+      load_words<B>(k0, true, tid, w0);
       load_digit(j, in);
     }
     if (j == own) {
+      if constexpr (DEEP) {
+        load_words<B>(k0, true, tid, w0);
+        load_words<B>(k1, true, tid, w1);
+      }
 #pragma unroll
       for (int e = 0; e < B::E; ++e) cur[e] = u2d(in[e]);
     } else {
 #pragma unroll
       for (int e = 0; e < B::E; ++e) cur[e] = raw2d(in[e]);
-      fwd_opaque<B, TWL>(A, cur, ld, tid, G0);
+      fwd_opaque<B, TWL>(A, cur, ld, tid, G0, [&](int r) {
+        if constexpr (DEEP) {
+          if (r == (B::NR > 2 ? B::NR - 2 : 1)) load_words<B>(k0, true, tid, w0);
+          if (r == B::NR - 1) load_words<B>(k1, true, tid, w1);
+        }
+      });
     }
     if constexpr (!DEEP) load_words<B>(k1, true, tid, w1);
 #pragma unroll
