@@ -78,12 +78,33 @@ __device__ __forceinline__ void inv_opaque(const Ar& A, typename Ar::T* v, typen
   B::template inv<REUSE>(A, v, ld, t, B0);
 }
 
+// A word of an intermediate of the KeySwitch that one workgroup reads, once: a
+// non-temporal load, first to leave the L2, so that what is read again (the key for
+// the items of a tile, tables) and what the kernel before wrote for the next one stays.
+// (4, 2^16, 32), one ciphertext, 149 -> 141 us, batch 8, 785 -> 774; (2, 2^15, 10),
+// batch 32, 422 -> 408. Not for the key: level 13 of (4, 2^16, 32), batch 3, 151 -> 158;
+// nor for d and the transforms in place: (2, 2^15, 10), batch 32, 418.
+__device__ __forceinline__ uint64_t ld_once(const uint64_t* p) { return __builtin_nontemporal_load(p); }
+
+// Column kernels with ONCE false are for a launch over a chunk of the targets, which
+// leaves the sources in the caches for the next chunk's launch: (2, 2^15, 10), batch 8,
+// DPOC with 4 chunks, 241 us, with non-temporal loads 247. (A branch in the kernel
+// costs the others 1%.)
+template <bool ONCE>
+__device__ __forceinline__ uint64_t ld_col(const uint64_t* p) {
+  if constexpr (ONCE)
+    return ld_once(p);
+  else
+    return *p;
+}
+
 // The E words of a thread of a block of M words at `src`, in the FR or CL
 // layout, as they are in memory: kernels that load ahead of use convert them
 // where they use them, since a conversion at the load would wait for it. Buffer
 // loads keep every address but one 32-bit offset in scalar registers, and that
 // offset is recomputed for each call (the hidden thread index) instead of being
-// held through the transforms.
+// held through the transforms. Words in the FR layout are an intermediate's, read
+// this once (see ld_once); the key, the twiddles and d are read by several workgroups.
 template <class B>
 __device__ __forceinline__ void load_words(const uint64_t* src, bool cl, int tid, uint64_t (&w)[B::E]) {
   typedef unsigned int v2u __attribute__((ext_vector_type(2)));
@@ -94,7 +115,11 @@ __device__ __forceinline__ void load_words(const uint64_t* src, bool cl, int tid
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t*>(src), 0, B::M * 8, 0x00027000);
 #pragma unroll
   for (int i = 0; i < B::E; ++i) {
-    const v2u v = __builtin_amdgcn_raw_buffer_load_b64(rs, base, 8 * (cl ? B::cl_step(i) : B::fr_step(i)), 0);
+    v2u v;
+    if (cl)
+      v = __builtin_amdgcn_raw_buffer_load_b64(rs, base, 8 * B::cl_step(i), 0);
+    else
+      v = __builtin_amdgcn_raw_buffer_load_b64(rs, base, 8 * B::fr_step(i), 2);  // non-temporal
     w[i] = ((uint64_t)v.y << 32) | v.x;
   }
 }
@@ -698,7 +723,7 @@ constexpr int mx_waves(int logr, int nm) { return logr <= 4 && mx_lds(logr, nm) 
 // w/2 + 4, ...; with 32 the groups w, w + 8, ...: per digit the Q targets outside
 // D_j in groups of four (in basis order), then the P targets. With `parts` > 1 that
 // many workgroups share a tile's groups, each with its own phase 1 (mx_parts).
-template <int LOGR, int NM>
+template <int LOGR, int NM, bool ONCE>
 __global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_modup_cols_mx(DevTables tb, const uint64_t* t1, uint64_t* ext1, int j0,
                                                      int nslots, int slot_stride, int tgt0, int tgt1, int log_m,
                                                      int parts) {
@@ -727,7 +752,7 @@ __global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_modup_cols_mx(DevTab
       const uint64_t* a = t1 + ((size_t)item * ell + i) * N + (C == 64 || live ? c : M - 1) + (size_t)(ph * RL) * M;
       double v[RL];
 #pragma unroll
-      for (int r = 0; r < RL; ++r) v[r] = raw2d(a[(size_t)r * M]);
+      for (int r = 0; r < RL; ++r) v[r] = raw2d(ld_col<ONCE>(a + (size_t)r * M));
       mx_inv<LOGR, C>(arf(tb, L, i, true), v, ph);
       const double w = tb.up_pre_d[i];
 #pragma unroll
@@ -1004,7 +1029,7 @@ __global__ __launch_bounds__(CT, LOGR <= 4 ? 4 : 2) void k_moddown_cols(DevTable
 // k_moddown_cols, canonical y packed into LDS ([pair][R][columns] x 16 bytes,
 // zero past the k sources and for columns past M). Phase 2: the groups of four Q
 // limbs that meet [tgt0, tgt1), shared out as in k_modup_cols_mx; output t2 raw.
-template <int LOGR, int NM>
+template <int LOGR, int NM, bool ONCE>
 __global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_moddown_cols_mx(DevTables tb, const uint64_t* accp, uint64_t* t2, int tgt0,
                                                        int tgt1, int log_m, int parts) {
   constexpr int R = 1 << LOGR, C = mx_cols(LOGR, NM), RL = mx_rows<LOGR, C>();
@@ -1029,7 +1054,7 @@ __global__ __launch_bounds__(CT, mx_waves(LOGR, NM)) void k_moddown_cols_mx(DevT
           accp + (((size_t)item * 2 + comp) * nl + ell + m) * N + (C == 64 || live ? c : M - 1) + (size_t)(ph * RL) * M;
       uint64_t v[RL];
 #pragma unroll
-      for (int r = 0; r < RL; ++r) v[r] = a[(size_t)r * M];
+      for (int r = 0; r < RL; ++r) v[r] = ld_col<ONCE>(a + (size_t)r * M);
       mx_inv<LOGR, C>(ari(tb, L, ell + m, true), v, ph);
       const uint64_t w = tb.dn_pre[2 * m], ws = tb.dn_pre[2 * m + 1];
 #pragma unroll
@@ -1084,7 +1109,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_blocks(DevTabl
   const uint64_t* src = t2 + ((size_t)ic * tb.ell + i) * N + boff;
   double v[B::E];
 #pragma unroll
-  for (int e = 0; e < B::E; ++e) v[e] = raw2d(src[B::fr_pos(tid, e)]);
+  for (int e = 0; e < B::E; ++e) v[e] = raw2d(ld_once(src + B::fr_pos(tid, e)));
   B::fwd(arf(tb, L, i, false), v, reinterpret_cast<double*>(lds), tid, B0);
   const uint64_t* a = acc + ((size_t)ic * tb.nl + i) * N + boff;
   uint64_t* o = out + ((size_t)ic * tb.ell + i) * N + boff;
@@ -1386,7 +1411,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE))) void k_moddown_pre(DevTables 
   {
     const uint64_t* src = t2 + (((size_t)item * 2 + c) * ell + i) * N + boff;
 #pragma unroll
-    for (int e = 0; e < B::E; ++e) v[e] = raw2d(src[B::fr_pos(tid, e)]);
+    for (int e = 0; e < B::E; ++e) v[e] = raw2d(ld_once(src + B::fr_pos(tid, e)));
   }
   B::fwd(arf(tb, L, i, false), v, reinterpret_cast<double*>(lds), tid, (uint32_t)R + b);
   double sum[B::E];
@@ -1903,13 +1928,14 @@ template <int LOGR, int NM>
 struct ModupColsMxN {
   static hipError_t run(const DevTables& tb, const uint64_t* t1, uint64_t* ext1, int j0, int nj, int nslots,
                         int slot_stride, int tgt0, int tgt1, int items, int log_m, hipStream_t s) {
-    allow_lds<k_modup_cols_mx<LOGR, NM>>();
+    const auto kernel = tgt0 == 0 && tgt1 == tb.nl ? k_modup_cols_mx<LOGR, NM, true> : k_modup_cols_mx<LOGR, NM, false>;
+    allow_lds<k_modup_cols_mx<LOGR, NM, true>>();
+    allow_lds<k_modup_cols_mx<LOGR, NM, false>>();
     dim3 g = col_grid(log_m, nj, items, mx_cols(LOGR, NM));
     const int na = tb.alpha < tb.ell ? tb.alpha : tb.ell;
     const int parts = mx_parts((long)g.x * g.y * g.z, (tb.ell - na + 3) / 4 + (tb.k + 3) / 4, mx_cols(LOGR, NM));
     g.x *= parts;
-    k_modup_cols_mx<LOGR, NM><<<g, dim3(CT), mx_lds(LOGR, NM), s>>>(tb, t1, ext1, j0, nslots, slot_stride, tgt0, tgt1,
-                                                                    log_m, parts);
+    kernel<<<g, dim3(CT), mx_lds(LOGR, NM), s>>>(tb, t1, ext1, j0, nslots, slot_stride, tgt0, tgt1, log_m, parts);
     return hipGetLastError();
   }
 };
@@ -1961,11 +1987,14 @@ template <int LOGR, int NM>
 struct ModdownColsMxN {
   static hipError_t run(const DevTables& tb, const uint64_t* accp, uint64_t* t2, int tgt0, int tgt1, int items,
                         int log_m, hipStream_t s) {
-    allow_lds<k_moddown_cols_mx<LOGR, NM>>();
+    const auto kernel =
+        tgt0 == 0 && tgt1 == tb.ell ? k_moddown_cols_mx<LOGR, NM, true> : k_moddown_cols_mx<LOGR, NM, false>;
+    allow_lds<k_moddown_cols_mx<LOGR, NM, true>>();
+    allow_lds<k_moddown_cols_mx<LOGR, NM, false>>();
     dim3 g = col_grid(log_m, 2, items, mx_cols(LOGR, NM));
     const int parts = mx_parts((long)g.x * g.y * g.z, (tgt1 - tgt0 + 3) / 4, mx_cols(LOGR, NM));
     g.x *= parts;
-    k_moddown_cols_mx<LOGR, NM><<<g, dim3(CT), mx_lds(LOGR, NM), s>>>(tb, accp, t2, tgt0, tgt1, log_m, parts);
+    kernel<<<g, dim3(CT), mx_lds(LOGR, NM), s>>>(tb, accp, t2, tgt0, tgt1, log_m, parts);
     return hipGetLastError();
   }
 };
