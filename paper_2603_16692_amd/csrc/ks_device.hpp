@@ -402,6 +402,15 @@ __device__ __forceinline__ int lds_pad(int x) { return x + (int)((unsigned)x >> 
 // 16-word line. The per-register offsets are then compile-time constants.
 __device__ constexpr int pad_step(int d) { return d + (d >> 4); }
 
+// Orders this wavefront's memory accesses before this point against those after
+// it. Its LDS accesses execute in order, so that no instruction is needed: it keeps
+// the compiler from moving one past another of a different type or lane.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Transform stages log_r .. log_n-1 (forward) of one contiguous block of
 // M = 2^LOGM elements, block index b in [0, R). T = M / E threads, E = 2^LOGE
 // elements per thread, done in rounds of LOGE stages (the first round takes
@@ -523,16 +532,12 @@ struct BlockNtt {
     return T <= 64 || ((q >= 1 || K1 == LOGE) && round_l(q) <= 64);
   }
   // Orders the LDS stores before this point against the loads after it: for
-  // the whole workgroup, or (local) for this wavefront, whose LDS accesses
-  // execute in order.
+  // the whole workgroup, or (local) for this wavefront.
   __device__ static __forceinline__ void exchange_sync(bool local) {
-    if (local) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    } else {
+    if (local)
+      wave_sync();
+    else
       __syncthreads();
-    }
   }
 
   // Forward: x enters in FR, leaves in CL. G0 = R + b. REUSE: a previous call

@@ -651,11 +651,12 @@ __device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2*
   const mx_tw<QG>*wa, *wb;
   if constexpr (mx_twl(LOGR)) {
     if constexpr (!CONV && PASS != 1) {
+      // the words hold the twiddles of the wave's group before, of another type if that
+      // was the last Q group: its reads come first
+      wave_sync();
 #pragma unroll
       for (int n = 0; n < mx_nt(LOGR); ++n) tw[lane + 64 * n] = wl[n];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      wave_sync();
     }
     wa = tw + (size_t)(2 * h) * R;
     wb = tw + (size_t)(2 * h + 1) * R;
