@@ -2125,6 +2125,20 @@ inline bool mx_auto(int count, int nm, int log_r) {
   return count >= 4 && nm <= mx_max_nm(log_r) && mx_lds(log_r, nm) <= 160 * 1024;
 }
 
+// ks_bconv calls that stay on the scalar kernel though mx_auto holds. The matrix kernel's
+// chain (scale, pack, a barrier, the constants, the folds) takes 6.1 us (4.0 from P,
+// which has no P targets to fold) at the smallest sizes; the scalar one's grows with the sources and, from about 2^20
+// products on, with the products. us, scalar / matrix, 4 sources: 0.5 M products 3.8 /
+// 6.5, 2.1 M 6.8 / 7.1, 4.2 M 11.1 / 8.9; 8 sources: 0.5 M 5.7 / 7.1, 2.1 M 7.0 / 7.4,
+// 4.2 M 10.3 / 7.8; 12 sources, up to 1.2 M, 3% apart, and 16, 10% slower; from P, 4 sources: 0.5 M
+// 3.8 / 4.5, 1.05 M 4.7 / 4.7, 2.1 M 6.8 / 5.1; 6 sources, up to 0.9 M, equal; 8: 5.6 / 4.8.
+// Below N = 2^8 the matrix form's columns are mostly empty: N = 2^6, 16 sources, 7.5 /
+// 9.2, from P, 8 sources, 4.8 / 5.2 (and 24 sources, 12 from P, faster there too).
+inline bool bconv_small(bool from_p, int ns, int log_n, long products) {
+  if (from_p) return ns <= (log_n < 8 ? 8 : 6) && products <= (1L << 20);
+  return ns <= (log_n < 8 ? 16 : 12) && products <= (5L << 19);
+}
+
 hipError_t launch_ntt(const DevTables& tb, int log_r, uint64_t* x, int first, int nlimbs, int items, hipStream_t s) {
   const int log_m = tb.log_n - log_r;
   hipError_t e = hipSuccess;
@@ -2233,7 +2247,9 @@ hipError_t launch_bconv(const DevTables& tb, const uint64_t* src, int set, uint6
   }
   const int ns = tb.nl - (set < 0 ? tb.ell : nd);
   const int nm = set < 0 ? tb.dn_nm : tb.up_nm;
-  if (mx_auto(ns, nm, BC_LOGR)) return by_nm<BconvMxN, BC_LOGR>(nm, tb, src, set, dst, items, s);
+  const long products = (long)ns * nd * items << tb.log_n;
+  if (mx_auto(ns, nm, BC_LOGR) && !bconv_small(set < 0, ns, tb.log_n, products))
+    return by_nm<BconvMxN, BC_LOGR>(nm, tb, src, set, dst, items, s);
   k_bconv<<<dim3((n + 255) / 256, nd, items), dim3(256), 0, s>>>(tb, src, dst, set);
   return hipGetLastError();
 }

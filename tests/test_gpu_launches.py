@@ -1,0 +1,39 @@
+"""Which kernels the library launches, where a rule on sizes chooses.
+
+The rules choose between kernels that give the same words, so comparing results cannot
+show that a call takes the wrong one; these tests read the launches of a captured call. Where
+a line divides two kernels, the calls on both sides of it are compared with the
+oracle bit for bit as well.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from synth import uniform_residues
+
+from gpu_util import dev, empty, first_mismatch, host, kernel_launches
+
+pytestmark = pytest.mark.gpu
+
+
+# (dnum, log_n, ell, source set, batch): the products sources x targets x N x batch on either
+# side of 5 * 2^19 from a digit (4 and 12 sources) and of 2^20 from P (4 and 6), and the
+# numbers of sources just past those that have a line (16 and 8 below N = 2^8)
+@pytest.mark.parametrize("dnum,log_n,ell,src,batch,kernel", [
+    (1, 3, 4, 0, 1, "k_bconv"), (2, 13, 8, 0, 9, "k_bconv"), (2, 13, 8, 0, 11, "k_bconv_mx"),
+    (2, 12, 24, 0, 2, "k_bconv"), (2, 12, 24, 0, 3, "k_bconv_mx"), (2, 8, 26, 1, 1, "k_bconv_mx"),
+    (1, 6, 16, 0, 2, "k_bconv"), (1, 7, 17, 0, 1, "k_bconv_mx"),
+    (2, 13, 8, -1, 4, "k_bconv"), (2, 13, 8, -1, 5, "k_bconv_mx"), (3, 12, 18, -1, 2, "k_bconv"),
+    (3, 12, 18, -1, 3, "k_bconv_mx"), (1, 8, 7, -1, 1, "k_bconv_mx"), (1, 7, 8, -1, 2, "k_bconv"),
+    (1, 6, 9, -1, 1, "k_bconv_mx"), (2, 13, 6, 0, 40, "k_bconv")])
+def test_bconv_by_size(dnum, log_n, ell, src, batch, kernel):
+    import paper_2603_16692_amd as ks
+    G, P = ks.KsParams(dnum, log_n, ell), oracle.Params(dnum, log_n, ell)
+    mods = P.p if src < 0 else [P.moduli[i] for i in P.digit(src)]
+    x = np.stack([uniform_residues(90 + b, mods, P.n) for b in range(batch)])
+    ref = oracle.bconv(P, src, x, batch)
+    xd, out = dev(x), empty(ref.shape)
+    launches = kernel_launches(lambda s: G.bconv(xd, src, out, batch, stream=s))
+    assert [k.name for k in launches] == [kernel]
+    mm = first_mismatch(host(out), ref)
+    assert mm is None, f"first mismatch {mm}"
