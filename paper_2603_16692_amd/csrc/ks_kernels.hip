@@ -1652,16 +1652,18 @@ __global__ __launch_bounds__(256) void k_add_q(DevTables tb, uint64_t* out, cons
   out[r] = v >= q ? v - q : v;
 }
 
-// ks_keymult: element-wise over acc [items][2][nl][N]. A thread takes 2 elements
+// ks_keymult: element-wise over acc [items][2][nl][N]. A thread takes E elements
 // (256 apart) of one limb for IT items and both components, so that ext is read
 // once and a key word once for IT items: it is bound by those bytes (420 MB for
 // two items of (4, 2^16, 32); one item and component a thread read 588 MB). Q limbs
 // on FP64 (canonical operands: each product within 0.88q), P limbs with p_mul.
-// Grid: (ceil(N / 512), nl, ceil(items / IT)).
-template <int IT>
+// Small calls are bound by a thread's chain over the digits instead, and take E = IT = 1
+// (see launch_keymult); there the next digit's loads go out with the current one's.
+// Grid: (ceil(N / (256 E)), nl, ceil(items / IT)).
+template <int IT, int E>
 __global__ __launch_bounds__(256) void k_keymult(DevTables tb, const uint64_t* ext, const uint64_t* evk,
                                                  uint64_t* acc, int items) {
-  constexpr int E = 2;
+  constexpr int UNROLL = IT * E == 1 ? 2 : 1;
   const size_t N = (size_t)1 << tb.log_n;
   const size_t x0 = (size_t)blockIdx.x * (256 * E) + threadIdx.x;
   const int t = blockIdx.y, i0 = blockIdx.z * IT, nl = tb.nl, ndig = tb.ndig;
@@ -1697,6 +1699,7 @@ __global__ __launch_bounds__(256) void k_keymult(DevTables tb, const uint64_t* e
   };
   uint64_t kw[2][E], w[IT][E];
   if (isq) {
+#pragma unroll UNROLL
     for (int j = 0; j < ndig; ++j) {
       load(j, kw, w);
 #pragma unroll
@@ -1710,6 +1713,7 @@ __global__ __launch_bounds__(256) void k_keymult(DevTables tb, const uint64_t* e
           }
     }
   } else {
+#pragma unroll UNROLL
     for (int j = 0; j < ndig; ++j) {
       load(j, kw, w);
 #pragma unroll
@@ -2393,11 +2397,27 @@ hipError_t launch_copy_rate(int kind, int nt, int blocks, const uint64_t* src, u
 
 hipError_t launch_keymult(const DevTables& tb, const uint64_t* ext, const uint64_t* evk, uint64_t* acc, int items,
                           hipStream_t s) {
-  const unsigned n = 1u << tb.log_n, gx = (n + 511) / 512;
-  if (items == 1)
-    k_keymult<1><<<dim3(gx, tb.nl, 1), dim3(256), 0, s>>>(tb, ext, evk, acc, items);
+  auto launch = [&](auto it, auto e) {
+    constexpr int IT = decltype(it)::value, E = decltype(e)::value;
+    const unsigned n = 1u << tb.log_n;
+    k_keymult<IT, E><<<dim3((n + 256 * E - 1) / (256 * E), tb.nl, (items + IT - 1) / IT), dim3(256), 0, s>>>(
+        tb, ext, evk, acc, items);
+  };
+  using One = std::integral_constant<int, 1>;
+  using Two = std::integral_constant<int, 2>;
+  // Below 3 * 2^18 coefficients of acc (at most 3 wavefronts for each SIMD with one a thread)
+  // every thread counts more than a key word read twice, as long as ext (2^22 words) fits
+  // the L2s. us, one coefficient / two / two for two items: (2, 2^10, 10), batch 4 (61 K),
+  // 2.7 / 3.4 / 4.2; (4, 2^13, 16), batch 2 (328 K), 5.1 / 6.3 / 7.3; (2, 2^12, 10), batch 16
+  // (983 K), 7.8 / 8.5 / 8.3; with 8 digits, (8, 2^13, 24), batch 3 (664 K, ext 5.3 M),
+  // 19.9 / 17.6 / 17.8, and (8, 2^14, 24), batch 2 (885 K, 7.1 M), 28 / 27 / 23.
+  const size_t words = (size_t)items * tb.nl << tb.log_n;
+  if (words < ((size_t)3 << 18) && words * tb.ndig < ((size_t)1 << 22))
+    launch(One{}, One{});
+  else if (items == 1)
+    launch(One{}, Two{});
   else
-    k_keymult<2><<<dim3(gx, tb.nl, (items + 1) / 2), dim3(256), 0, s>>>(tb, ext, evk, acc, items);
+    launch(Two{}, Two{});
   return hipGetLastError();
 }
 

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 import oracle
-from synth import uniform_residues
+from synth import uniform_key, uniform_residues
 
 from gpu_util import dev, empty, first_mismatch, host, kernel_launches
 
@@ -36,4 +36,28 @@ def test_bconv_by_size(dnum, log_n, ell, src, batch, kernel):
     launches = kernel_launches(lambda s: G.bconv(xd, src, out, batch, stream=s))
     assert [k.name for k in launches] == [kernel]
     mm = first_mismatch(host(out), ref)
+    assert mm is None, f"first mismatch {mm}"
+
+
+# below 3 * 2^18 coefficients (batch x limbs x N), and 2^22 of ext, one item and one coefficient a thread, else two
+# coefficients, of two items where there are two; limbs shorter than a workgroup, a last odd
+# item, more digits than a sum holds unfolded (9, 10)
+@pytest.mark.parametrize("dnum,log_n,ell,batch,args", [
+    (2, 3, 4, 5, (1, 1)), (9, 8, 9, 3, (1, 1)), (10, 10, 10, 1, (1, 1)), (2, 13, 10, 6, (1, 1)),
+    (2, 16, 8, 1, (1, 2)), (2, 13, 8, 8, (2, 2)), (10, 13, 10, 9, (2, 2)),
+    (10, 12, 10, 9, (1, 1)), (10, 12, 10, 10, (2, 2))])
+def test_keymult_by_size(dnum, log_n, ell, batch, args):
+    import paper_2603_16692_amd as ks
+    G, P = ks.KsParams(dnum, log_n, ell), oracle.Params(dnum, log_n, ell)
+    ext = np.stack([[uniform_residues(70 + b * P.ndig + j, P.moduli, P.n) for j in range(P.ndig)]
+                    for b in range(batch)])
+    top = np.array(P.moduli, dtype=np.uint64)[:, None] - np.uint64(1)
+    ext[..., ::3] = top
+    evk = uniform_key(P.moduli, P.n, P.ndig)
+    evk[..., ::2] = top
+    ref = oracle.keymult(P, ext, evk, batch)
+    xd, kd, acc = dev(ext), dev(evk), empty(ref.shape)
+    launches = kernel_launches(lambda s: G.keymult(xd, kd, acc, batch, stream=s))
+    assert [(k.name, k.args) for k in launches] == [("k_keymult", args)]
+    mm = first_mismatch(host(acc), ref)
     assert mm is None, f"first mismatch {mm}"
