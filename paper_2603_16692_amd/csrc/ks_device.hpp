@@ -479,6 +479,7 @@ struct BlockNtt {
   // The twiddles of a round that is not uniform (LOGE stages, one subproblem a
   // thread), loaded before the exchange that precedes it. All rounds' together at
   // the start of the transform, where they fit the registers, measured the same.
+  // (AHEAD false: read where they are used, for a kernel that has no registers for them.)
   template <class Ar>
   struct TwRegs {
     typename Ar::TwT w[E - 1];
@@ -549,7 +550,7 @@ struct BlockNtt {
   struct Nothing {
     __device__ __forceinline__ void operator()(int) const {}
   };
-  template <bool STAGED = false, bool REUSE = false, class Ar, class H = Nothing>
+  template <bool STAGED = false, bool REUSE = false, bool AHEAD = true, class Ar, class H = Nothing>
   __device__ static __forceinline__ void fwd(const Ar& A, typename Ar::T* x, typename Ar::T* lds, int tid, uint32_t G0,
                                              H between = H()) {
     round0_fwd(A, x, tid, G0);
@@ -558,7 +559,7 @@ struct BlockNtt {
 #pragma unroll
     for (int r = 1; r < NR; ++r) {
       TwRegs<Ar> t;
-      if (!STAGED && !uniform(r)) load_round_tw(A, t, r, tid, G0);
+      if (AHEAD && !STAGED && !uniform(r)) load_round_tw(A, t, r, tid, G0);
       between(r);
       exchange_sync(wave_local(r - 1));
       from_lds<LOGE>(x, lds, r, tid);
@@ -568,6 +569,8 @@ struct BlockNtt {
         sub_fwd<LOGE, LAST_S0>(A, x, base(r, tid, 0, 1u));
       else if (STAGED)
         sub_fwd<LOGE>(A, x, base(r, tid, 0, 1u));
+      else if (!AHEAD)
+        sub_fwd<LOGE>(A, x, base(r, tid, 0, G0));
       else
         sub_fwd_by<LOGE>(A, x, [&](int rho, uint32_t g) { return t.w[(1 << rho) - 1 + g]; });
       to_lds<LOGE>(x, lds, r, tid);
@@ -579,7 +582,7 @@ struct BlockNtt {
   }
 
   // Inverse: x enters in CL, leaves in FR. REUSE as in fwd.
-  template <bool REUSE = false, class Ar>
+  template <bool REUSE = false, bool AHEAD = true, class Ar>
   __device__ static void inv(const Ar& A, typename Ar::T* x, typename Ar::T* lds, int tid, uint32_t G0) {
     if (REUSE) __syncthreads();
     typename Ar::T* c = lds + lds_pad(cl_base(tid));
@@ -588,11 +591,13 @@ struct BlockNtt {
 #pragma unroll
     for (int r = NR - 1; r >= 1; --r) {
       TwRegs<Ar> t;
-      if (!uniform(r)) load_round_tw(A, t, r, tid, G0);
+      if (AHEAD && !uniform(r)) load_round_tw(A, t, r, tid, G0);
       exchange_sync(r == NR - 1 || wave_local(r));  // the first read follows the CL stores
       from_lds<LOGE>(x, lds, r, tid);
       if (uniform(r))
         sub_inv<LOGE, true>(A, x, base(r, tid, 0, G0));
+      else if (!AHEAD)
+        sub_inv<LOGE>(A, x, base(r, tid, 0, G0));
       else
         sub_inv_by<LOGE>(A, x, [&](int rho, uint32_t g) { return t.w[(1 << rho) - 1 + g]; });
       to_lds<LOGE>(x, lds, r, tid);

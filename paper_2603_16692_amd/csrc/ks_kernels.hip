@@ -63,19 +63,19 @@ inline unsigned xcd_grid(int ntiles, int items) { return (unsigned)(((ntiles + 7
 // runs several transforms would otherwise keep every LDS and twiddle address
 // of all rounds live from the first transform to the last, which costs more
 // registers than recomputing them.
-template <class B, bool STAGED = false, bool REUSE = true, class Ar, class H = typename B::Nothing>
+template <class B, bool STAGED = false, bool REUSE = true, bool AHEAD = true, class Ar, class H = typename B::Nothing>
 __device__ __forceinline__ void fwd_opaque(const Ar& A, typename Ar::T* v, typename Ar::T* ld, int tid, uint32_t B0,
                                            H between = H()) {
   int t = tid;
   asm volatile("" : "+v"(t));
-  B::template fwd<STAGED, REUSE>(A, v, ld, t, B0, between);
+  B::template fwd<STAGED, REUSE, AHEAD>(A, v, ld, t, B0, between);
 }
-template <class B, bool REUSE = true, class Ar>
+template <class B, bool REUSE = true, bool AHEAD = true, class Ar>
 __device__ __forceinline__ void inv_opaque(const Ar& A, typename Ar::T* v, typename Ar::T* ld, int tid,
                                            uint32_t B0) {
   int t = tid;
   asm volatile("" : "+v"(t));
-  B::template inv<REUSE>(A, v, ld, t, B0);
+  B::template inv<REUSE, AHEAD>(A, v, ld, t, B0);
 }
 
 // A word of an intermediate of the KeySwitch that one workgroup reads, once: a
@@ -838,6 +838,10 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
   const size_t boff = (size_t)b * B::M;
   uint64_t* a0 = acc + (((size_t)item * 2 + 0) * nl + t) * N + boff;
   uint64_t* a1 = acc + (((size_t)item * 2 + 1) * nl + t) * N + boff;
+  // At blocks of 2^14 the 16 elements of both sums and of the transform fill the 128 registers of
+  // 1024 threads: the next input (P limbs) and a round's twiddles loaded ahead of use went to
+  // scratch memory (296 bytes a lane, now 96; (2, 2^17, 44), one ciphertext, 180 us, now 153).
+  constexpr bool AHEAD = LOGM <= 13;
   if constexpr (QPATH) {
     const ArF A = arf(tb, L, t, false);
     double* ld = reinterpret_cast<double*>(lds);
@@ -856,7 +860,7 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
         const uint64_t* src = ext1 + (((size_t)item * nslots + slot) * nl + t) * N + boff;
 #pragma unroll
         for (int i = 0; i < B::E; ++i) v[i] = raw2d(src[B::fr_pos(tid, i)]);
-        fwd_opaque<B>(A, v, ld, tid, B0);
+        fwd_opaque<B, false, true, AHEAD>(A, v, ld, tid, B0);
       }
       const uint64_t* k0 = evk + key_row(tb, j, 0, t) * N + boff;
       const uint64_t* k1 = evk + key_row(tb, j, 1, t) * N + boff;
@@ -900,14 +904,20 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
   auto load_digit = [&](int j, uint64_t (&w)[B::E]) {
     load_words<B>(ext1 + (((size_t)item * nslots + (slot_stride ? j : 0)) * nl + t) * N + boff, false, tid, w);
   };
-  uint64_t nxt[B::E];
-  if (j0 < j1) load_digit(j0, nxt);
+  uint64_t nxt[AHEAD ? B::E : 1];
+  if constexpr (AHEAD) {
+    if (j0 < j1) load_digit(j0, nxt);
+  }
   for (int j = j0; j < j1; ++j) {
     uint64_t w0[B::E], w1[B::E];
+    if constexpr (AHEAD) {
 #pragma unroll
-    for (int i = 0; i < B::E; ++i) v[i] = nxt[i];
-    if (j + 1 < j1) load_digit(j + 1, nxt);
-    fwd_opaque<B>(A, v, lds, tid, B0);
+      for (int i = 0; i < B::E; ++i) v[i] = nxt[i];
+      if (j + 1 < j1) load_digit(j + 1, nxt);
+    } else {
+      load_digit(j, v);
+    }
+    fwd_opaque<B, false, true, AHEAD>(A, v, lds, tid, B0);
     load_words<B>(evk + key_row(tb, j, 0, t) * N + boff, true, tid, w0);
     load_words<B>(evk + key_row(tb, j, 1, t) * N + boff, true, tid, w1);
     // each product is below 1.5 * 2^60: folded every 8 digits, the sums stay below 2^64
@@ -941,10 +951,10 @@ __global__ __launch_bounds__((1 << (LOGM - LOGE)), (LOGE == 3 && LOGM >= 12) ? 4
   }
   if (finalize) {
     const ArI Ai = ari(tb, L, t, true);
-    inv_opaque<B>(Ai, s0, lds, tid, B0);
+    inv_opaque<B, true, AHEAD>(Ai, s0, lds, tid, B0);
 #pragma unroll
     for (int i = 0; i < B::E; ++i) a0[B::fr_pos(tid, i)] = s0[i];
-    inv_opaque<B>(Ai, s1, lds, tid, B0);
+    inv_opaque<B, true, AHEAD>(Ai, s1, lds, tid, B0);
 #pragma unroll
     for (int i = 0; i < B::E; ++i) a1[B::fr_pos(tid, i)] = s1[i];
   } else {

@@ -61,3 +61,18 @@ def test_keymult_by_size(dnum, log_n, ell, batch, args):
     assert [(k.name, k.args) for k in launches] == [("k_keymult", args)]
     mm = first_mismatch(host(acc), ref)
     assert mm is None, f"first mismatch {mm}"
+
+
+# blocks of 2^14 run 16 elements on each of 1024 threads, which have 128 registers: what
+# KeyMult loads ahead of use beyond them only goes to scratch memory and back (bytes a lane)
+@pytest.mark.parametrize("dataflow", ["DPOB", "DSOB"])
+def test_keymult_scratch_memory_at_the_largest_blocks(dataflow):
+    import paper_2603_16692_amd as ks
+    G = ks.KsParams(2, 14, 4)
+    plan = ks.make_plan(getattr(ks, dataflow), 1, 0)
+    sh = G.shapes(1)
+    d, evk, out, ws = empty(sh["d"]).zero_(), empty(sh["evk"]).zero_(), empty(sh["out"]), G.workspace(1, plan)
+    found = [k for k in kernel_launches(lambda s: G.keyswitch(d, evk, out, 1, ws, plan, stream=s))
+             if k.name == "k_keymult_blocks"]
+    assert found and all(k.args[:2] == (14, 4) for k in found)
+    assert all(k.scratch <= 128 for k in found), found
