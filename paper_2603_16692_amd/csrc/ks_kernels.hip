@@ -567,8 +567,12 @@ __device__ __forceinline__ void mx_inv(const Ar& A, typename Ar::T (&v)[mx_rows<
 // so the stores are non-temporal (measured: 5% off the ModUp column kernel).
 template <bool QG>
 using mx_val = typename std::conditional<QG, double, uint64_t>::type;
+// (w, Shoup) as a vector type: an array of HIP's ulonglong2 structs with more than one entry
+// stays in scratch memory (48 bytes a lane at 32 rows; the times are within noise:
+// (8, 2^17, 56), batch 2, 1049 -> 1046 us).
+typedef uint64_t mx_v2u __attribute__((ext_vector_type(2)));
 template <bool QG>
-using mx_tw = typename std::conditional<QG, double, ulonglong2>::type;
+using mx_tw = typename std::conditional<QG, double, mx_v2u>::type;
 
 // CONV: the conversion alone (ks_bconv): no transform, canonical words.
 template <int LOGR, bool QG, bool CONV>
@@ -665,7 +669,7 @@ __device__ __forceinline__ void mx_target(const DevTables& tb, const ulonglong2*
     if constexpr (QG)
       tab = tb.twf_d;
     else
-      tab = reinterpret_cast<const ulonglong2*>(tb.twf);
+      tab = reinterpret_cast<const mx_v2u*>(tb.twf);
     wa = tab + ((size_t)ta << tb.log_n);
     wb = tab + ((size_t)tc << tb.log_n);
   }
@@ -696,7 +700,7 @@ __device__ __forceinline__ void mx_group(const DevTables& tb, const ulonglong2* 
       if constexpr (QG)
         wl[n] = tb.twf_d[x];
       else
-        wl[n] = reinterpret_cast<const ulonglong2*>(tb.twf)[x];
+        wl[n] = reinterpret_cast<const mx_v2u*>(tb.twf)[x];
     }
   }
   ulonglong2 cst[NM];

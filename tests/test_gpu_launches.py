@@ -76,3 +76,18 @@ def test_keymult_scratch_memory_at_the_largest_blocks(dataflow):
              if k.name == "k_keymult_blocks"]
     assert found and all(k.args[:2] == (14, 4) for k in found)
     assert all(k.scratch <= 128 for k in found), found
+
+
+# the column kernels with 32 rows keep everything in registers (1, 2, 3 steps of four
+# sources: 64 columns and 32)
+@pytest.mark.parametrize("ell", [8, 16, 20])
+def test_column_kernels_of_32_rows_use_no_scratch_memory(ell):
+    import paper_2603_16692_amd as ks
+    G = ks.KsParams(2, 8, ell)
+    plan = ks.make_plan(ks.DPOB, 1, 5)
+    sh = G.shapes(1)
+    d, evk, out, ws = empty(sh["d"]).zero_(), empty(sh["evk"]).zero_(), empty(sh["out"]), G.workspace(1, plan)
+    found = [k for k in kernel_launches(lambda s: G.keyswitch(d, evk, out, 1, ws, plan, stream=s))
+             if k.name in ("k_modup_cols_mx", "k_moddown_cols_mx")]
+    assert [k.args[:2] for k in found] == [(5, -(-ell // 8))] * 2
+    assert not any(k.scratch for k in found), found
