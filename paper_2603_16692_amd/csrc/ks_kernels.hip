@@ -1923,9 +1923,9 @@ struct ModupCols {
     return hipGetLastError();
   }
 };
-// Steps (of four sources) an MFMA column kernel is built for: 8, or fewer where
-// its digits would not fit 160 KB of LDS.
-constexpr int mx_max_nm(int logr) { return logr <= 4 ? 8 : 4; }
+// Steps (of four sources) an MFMA column kernel is built for: 8, or fewer at the row
+// counts for which a plan is accepted with fewer sources only (stage_cap: at most 320 / 2^logr).
+constexpr int mx_max_nm(int logr) { return logr <= 3 ? 8 : (logr == 4 ? 5 : 3); }
 
 // F<LOGR, nm>::run for a runtime nm.
 template <template <int, int> class F, int LOGR, int NM = 1, typename... A>
