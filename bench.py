@@ -512,7 +512,7 @@ def main():
     roofline_alu = None
     nmm = kernel_modmuls(G, plan, batch, dominant) if args.op == "keyswitch" else None
     if nmm is not None:
-        peaks = {name: G.modmul_rate(kind) / 1e12 for kind, name in ((0, "fp64"), (1, "shoup"), (2, "montgomery"))}
+        peaks = {name: G.modmul_rate(kind) / 1e12 for kind, name in ((0, "fp64"), (1, "p_constant"), (2, "p_variable"))}
         rate = nmm / per_step / (dom_avg_ms / 1e3) / 1e12
         roofline_alu = {"bound": "alu", "achieved": round(rate, 3), "peak": round(peaks["fp64"], 3),
                         "unit": "T modmul/s", "frac": round(rate / peaks["fp64"], 4), "kernel": ks.KIND_NAMES[dominant],

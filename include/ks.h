@@ -307,8 +307,9 @@ int ks_trace_end(int* kinds, int capacity);
  * ALU roofline of the path): blocks x 256 threads each run ks_modmul_chains()
  * independent chains of `iters` dependent products by a fixed residue, for
  * kind 0 the FP64 product modulo the first Q prime (the Q-limb arithmetic),
- * 1 the Shoup product and 2 the Montgomery product modulo the first P prime
- * (the P-limb arithmetic); each thread writes one word of its result to
+ * and modulo the first P prime (the P-limb arithmetic) 1 the product by a
+ * constant with a precomputed quotient (the transforms) and 2 the product of two
+ * variables folded at 2^60 (KeyMult); each thread writes the canonical sum of its chains to
  * sink [blocks * 256] (a device buffer the caller owns). Time it with events
  * on `stream`: products = blocks * 256 * ks_modmul_chains() * iters.
  * KS_EINVAL for another kind, blocks outside [1, 2^20] or iters < 1. */

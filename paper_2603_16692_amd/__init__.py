@@ -323,8 +323,8 @@ class KsParams:
                             ctypes.byref(plan) if plan else None, _ptr(ws), _stream(stream)), "ks_hrot")
 
     def modmul_rate(self, kind: int, blocks: int = 4096, iters: int = 2048, reps: int = 3) -> float:
-        """Measured modular products per second of one kind (0 FP64, 1 Shoup,
-        2 Montgomery; ks_modmul_rate), the best of `reps` timed launches."""
+        """Measured modular products per second of one kind (0 FP64, 1 by a constant
+        and 2 of two variables modulo a P prime; ks_modmul_rate), the best of `reps` timed launches."""
         sink = torch.empty(blocks * 256, dtype=torch.int64, device="cuda")
         stream = torch.cuda.current_stream()
         ev = HipEvents(2)

@@ -840,8 +840,7 @@ int ks_modmul_rate(const ks_params* p, int kind, int blocks, int iters, uint64_t
   // the FP64 product on the first Q prime, the integer products on the first P prime
   const uint64_t q = p->hp.mod[kind == 0 ? 0 : p->hp.ell];
   const uint64_t w = q / 3 + 1;
-  KS_TRY(ks::launch_modmul_rate(kind, blocks, iters, q, w, ks::host_shoup(w, q), ks::host_mont_neg_inv(q), sink,
-                                (hipStream_t)stream));
+  KS_TRY(ks::launch_modmul_rate(kind, blocks, iters, q, w, ks::host_shoup(w, q), sink, (hipStream_t)stream));
   return KS_OK;
 }
 

@@ -133,14 +133,6 @@ __device__ __forceinline__ uint64_t p_mul(uint64_t a, uint64_t b, uint32_t delta
   return low + (uint64_t)(uint32_t)(u >> 28) * delta;
 }
 
-// Montgomery REDC of a*b for a*b < q * 2^64: returns a*b*2^-64 mod q in [0, 2q).
-__device__ __forceinline__ uint64_t mont_mul(uint64_t a, uint64_t b, uint64_t q, uint64_t ninv) {
-  const uint64_t lo = a * b, hi = __umul64hi(a, b);
-  const uint64_t m = lo * ninv;
-  const uint64_t mh = __umul64hi(m, q);
-  return hi + mh + (lo != 0 ? 1 : 0);
-}
-
 // --------------------------------------------------------------- FP64
 
 // a*b mod q as an integer-valued double with |r| <= q/2 + 1.5*2^-52*|a*b|,

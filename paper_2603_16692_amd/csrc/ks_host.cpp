@@ -87,13 +87,6 @@ uint32_t bitrev(uint32_t x, int bits) {
 
 uint64_t shoup(uint64_t w, uint64_t q) { return (uint64_t)(((u128)w << 64) / q); }
 
-// -q^-1 mod 2^64 by Newton's iteration (q odd).
-uint64_t mont_neg_inv(uint64_t q) {
-  uint64_t x = q;  // correct to 3 bits
-  for (int i = 0; i < 6; ++i) x *= 2 - q * x;
-  return ~x + 1;
-}
-
 size_t align_words(size_t w) { return (w + 31) & ~(size_t)31; }
 
 // Balanced base-256 digits of v < 2^60: v = sum_b d_b 256^b with d_b in
@@ -145,7 +138,6 @@ void mx_lane(uint64_t* out, int l, int m, int nsrc, Cst cst) {
 }  // namespace
 
 uint64_t host_shoup(uint64_t w, uint64_t q) { return shoup(w, q); }
-uint64_t host_mont_neg_inv(uint64_t q) { return mont_neg_inv(q); }
 
 bool derive_params(int dnum, int log_n, int ell, HostParams& hp) {
   if (log_n < 3 || log_n > 17 || ell < 1 || dnum < 1 || dnum > ell) return false;

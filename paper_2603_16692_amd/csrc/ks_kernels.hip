@@ -2304,13 +2304,14 @@ hipError_t launch_add_q(const DevTables& tb, uint64_t* out, const uint64_t* add,
 // Throughput probe of the three modular products the kernels are built
 // from. Every thread runs MM_CHAINS independent chains of `iters` dependent
 // products by a fixed operand (enough chains to hide the latency of one
-// product), then folds its chains into sink[thread] so that no product is
-// dead code. kind 0: FP64 product of the Q primes (f_mul); 1: Shoup product
-// of the P primes (mul_shoup); 2: Montgomery product (mont_mul).
+// product), then writes the canonical sum of its chains to sink[thread]. kind 0: FP64
+// product of the Q primes (f_mul); 1: product by a constant of the P primes
+// (mul_shoup_lazy); 2: product of two variables of the P primes, with the fold of one of
+// them that KeyMult does (p_red, p_mul).
 constexpr int MM_CHAINS = MODMUL_CHAINS;
 
 template <int KIND>
-__global__ __launch_bounds__(256) void k_modmul_rate(int iters, uint64_t q, uint64_t w, uint64_t ws, uint64_t ninv,
+__global__ __launch_bounds__(256) void k_modmul_rate(int iters, uint64_t q, uint64_t w, uint64_t ws, uint32_t delta,
                                                      double qd, double qinv, double wd, uint64_t* sink) {
   const uint32_t tid = blockIdx.x * 256u + threadIdx.x;
   if (KIND == 0) {
@@ -2331,24 +2332,26 @@ __global__ __launch_bounds__(256) void k_modmul_rate(int iters, uint64_t q, uint
     for (int c = 0; c < MM_CHAINS; ++c) a[c] = (uint64_t)(tid * MM_CHAINS + c + 1);
     for (int i = 0; i < iters; ++i) {
 #pragma unroll
-      for (int c = 0; c < MM_CHAINS; ++c) a[c] = KIND == 1 ? mul_shoup(a[c], w, ws, q) : mont_mul(a[c], w, q, ninv);
+      for (int c = 0; c < MM_CHAINS; ++c)
+        a[c] = KIND == 1 ? mul_shoup_lazy(a[c], w, ws, ~q + 1) : p_mul(p_red(a[c], delta), w, delta);
     }
     uint64_t acc = 0;
 #pragma unroll
-    for (int c = 0; c < MM_CHAINS; ++c) acc ^= a[c];
-    sink[tid] = acc;
+    for (int c = 0; c < MM_CHAINS; ++c) acc = p_red(acc + p_red(a[c], delta), delta);
+    sink[tid] = p_canon(acc, q, delta);
   }
 }
 
-hipError_t launch_modmul_rate(int kind, int blocks, int iters, uint64_t q, uint64_t w, uint64_t ws, uint64_t ninv,
-                              uint64_t* sink, hipStream_t s) {
+hipError_t launch_modmul_rate(int kind, int blocks, int iters, uint64_t q, uint64_t w, uint64_t ws, uint64_t* sink,
+                              hipStream_t s) {
   const double qd = (double)q, qinv = 1.0 / qd;
   // the fixed operand in balanced form for the FP64 product
   const double wd = w > q / 2 ? (double)w - qd : (double)w;
+  const uint32_t delta = (uint32_t)(((uint64_t)1 << 60) - q);  // P primes
   switch (kind) {
-    case 0: k_modmul_rate<0><<<dim3(blocks), dim3(256), 0, s>>>(iters, q, w, ws, ninv, qd, qinv, wd, sink); break;
-    case 1: k_modmul_rate<1><<<dim3(blocks), dim3(256), 0, s>>>(iters, q, w, ws, ninv, qd, qinv, wd, sink); break;
-    case 2: k_modmul_rate<2><<<dim3(blocks), dim3(256), 0, s>>>(iters, q, w, ws, ninv, qd, qinv, wd, sink); break;
+    case 0: k_modmul_rate<0><<<dim3(blocks), dim3(256), 0, s>>>(iters, q, w, ws, delta, qd, qinv, wd, sink); break;
+    case 1: k_modmul_rate<1><<<dim3(blocks), dim3(256), 0, s>>>(iters, q, w, ws, delta, qd, qinv, wd, sink); break;
+    case 2: k_modmul_rate<2><<<dim3(blocks), dim3(256), 0, s>>>(iters, q, w, ws, delta, qd, qinv, wd, sink); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -69,8 +69,8 @@ hipError_t launch_add_q(const DevTables& tb, uint64_t* out, const uint64_t* add,
 hipError_t launch_keymult(const DevTables& tb, const uint64_t* ext, const uint64_t* evk, uint64_t* acc, int items,
                           hipStream_t s);
 // Modular-product throughput probe: blocks x 256 threads x MODMUL_CHAINS chains x
-// iters products of kind 0 (FP64, modulus q < 2^50), 1 (Shoup) or 2
-// (Montgomery); sink [blocks * 256].
+// iters products of kind 0 (FP64, modulus q < 2^50), or of a P prime by a constant (1)
+// or of two variables (2); sink [blocks * 256].
 constexpr int MODMUL_CHAINS = 8;
 // Debug-build input check: *flag = 1 if a word of x [items][rows][N] (item
 // stride item_words) is not below the prime of its row (row_limb[r] < 0: skip).
@@ -80,7 +80,7 @@ hipError_t launch_check_rows(const DevTables& tb, const uint64_t* x, const int* 
 // or 16 (kind 1) bytes per access, non-temporal stores when nt != 0.
 hipError_t launch_copy_rate(int kind, int nt, int blocks, const uint64_t* src, uint64_t* dst, size_t words,
                             hipStream_t s);
-hipError_t launch_modmul_rate(int kind, int blocks, int iters, uint64_t q, uint64_t w, uint64_t ws, uint64_t ninv,
-                              uint64_t* sink, hipStream_t s);
+hipError_t launch_modmul_rate(int kind, int blocks, int iters, uint64_t q, uint64_t w, uint64_t ws, uint64_t* sink,
+                              hipStream_t s);
 
 }  // namespace ks
