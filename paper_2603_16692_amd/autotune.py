@@ -23,7 +23,7 @@ import statistics
 import torch
 
 from . import (DPOB, DPOC, DSOB, DSOC, STAGED, DATAFLOW_NAMES, HipEvents,
-               KsError, PLAN_HOIST_FWD, Plan, make_plan)
+               KsError, PLAN_HOIST_FWD, PLAN_MFMA_BCONV, Plan, make_plan)
 
 WORD = 8
 MALL_BYTES = 256 << 20
@@ -44,8 +44,8 @@ def footprint_bytes(dnum: int, n: int, ell: int, dataflow: int, chunks: int = 1,
 
 
 def candidate_plans(params, batch: int, chunk_range=CHUNK_RANGE, mfma=(False, True), split=None, tiles=None):
-    """Every plan libks accepts for these parameters and batch, with the
-    FP64 / integer BConv and with the int8-MFMA BConv, and (batch >= 2) with
+    """Every plan libks accepts for these parameters and batch, without and with the
+    flag that asks for the int8-MFMA BConv, and (batch >= 2) with
     the batch on one stream or split over two; for batch >= 4 also the
     digit-parallel plans (DPOB, STAGED) run in passes of batch/2 and batch/4
     items, whose footprint is that of the smaller pass (the batch tile)."""
@@ -78,6 +78,17 @@ def candidate_plans(params, batch: int, chunk_range=CHUNK_RANGE, mfma=(False, Tr
         except KsError:
             pass
     return valid
+
+
+def distinct_plans(params, plans):
+    """`plans` without those that launch the same kernels as another one: where a
+    digit has 4 primes or more, every BConv runs on the matrix cores with or
+    without PLAN_MFMA_BCONV, and the plan without the flag stands for both."""
+    if min(params.alpha, params.ell) < 4:
+        return list(plans)
+    keys = {p.key() for p in plans}
+    twin = lambda k: (k[0], k[1], k[2], k[3] & ~PLAN_MFMA_BCONV, k[4])
+    return [p for p in plans if not p.flags & PLAN_MFMA_BCONV or twin(p.key()) not in keys]
 
 
 def prior_order(params, batch: int, plans, cache_bytes: int = MALL_BYTES):
@@ -165,7 +176,7 @@ def tune(params, d, evk, batch: int, plans=None, reps: int = 5, trials: int = 3,
     plan) over an equally fast earlier one. With `cache`, the winner is
     stored under this device, ROCm version, parameter set and batch."""
     if plans is None:
-        plans = prior_order(params, batch, candidate_plans(params, batch))
+        plans = prior_order(params, batch, distinct_plans(params, candidate_plans(params, batch)))
     if max_plans:
         plans = plans[:max_plans]
     out = torch.empty((batch, 2, params.ell, params.n), dtype=torch.int64, device=d.device)
@@ -251,7 +262,7 @@ def grid_map(batch: int = 1, chunk_range=(2, 4, 8), reps: int = 3, trials: int =
                 G = KsParams(dnum, log_n, ell)
                 d = dev(ciphertext_batch(G.moduli[:ell], G.n, batch))
                 evk = dev(uniform_key(G.moduli, G.n, G.ndig))
-                plans = prior_order(G, batch, candidate_plans(G, batch, chunk_range))
+                plans = prior_order(G, batch, distinct_plans(G, candidate_plans(G, batch, chunk_range)))
                 best, results = tune(G, d, evk, batch, plans=plans, reps=reps, trials=trials, cache=table)
                 per_df = {}
                 for r in results:

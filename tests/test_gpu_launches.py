@@ -91,3 +91,26 @@ def test_column_kernels_of_32_rows_use_no_scratch_memory(ell):
              if k.name in ("k_modup_cols_mx", "k_moddown_cols_mx")]
     assert [k.args[:2] for k in found] == [(5, -(-ell // 8))] * 2
     assert not any(k.scratch for k in found), found
+
+
+# the tuner leaves out the plan with the matrix-core flag where distinct_plans says that it
+# launches what the plan without it does
+@pytest.mark.parametrize("dnum,log_n,ell,level", [(2, 9, 8, 8), (2, 9, 6, 6), (1, 9, 16, 16), (2, 9, 16, 4),
+                                                  (2, 9, 16, 3)])
+def test_flag_twins_launch_the_same_kernels(dnum, log_n, ell, level):
+    import paper_2603_16692_amd as ks
+    from paper_2603_16692_amd import autotune
+    top = ks.KsParams(dnum, log_n, ell)
+    G = top if level == ell else top.at_level(level)
+    d, evk, out = empty(G.shapes(2)["d"]).zero_(), empty(top.shapes(1)["evk"]).zero_(), empty(G.shapes(2)["out"])
+
+    def launches(plan):
+        ws = G.workspace(2, plan)
+        return kernel_launches(lambda s: G.keyswitch(d, evk, out, 2, ws, plan, stream=s))
+
+    plans = [p for p in autotune.candidate_plans(G, 2, chunk_range=(2,)) if p.flags & ks.PLAN_MFMA_BCONV]
+    kept = {p.key() for p in autotune.distinct_plans(G, autotune.candidate_plans(G, 2, chunk_range=(2,)))}
+    assert plans
+    for p in plans:
+        twin = ks.Plan(p.dataflow, p.chunks, p.log_r, p.flags & ~ks.PLAN_MFMA_BCONV, p.batch_tile)
+        assert (launches(p) == launches(twin)) == (p.key() not in kept), p
