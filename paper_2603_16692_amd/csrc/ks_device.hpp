@@ -6,10 +6,10 @@
 //    h = fl(a*b), l = fma(a, b, -h) gives p = h + l exactly; k = rint(h * fl(1/q))
 //    is within 1/2 + 1.5*2^-52*|p|/q of p/q, and r = fma(-k, q, h) + l = p - k*q
 //    exactly whenever |p| <= 2^103. So |r| <= q/2 + 1.5*2^-52*|p|. The
-//    transform keeps every value within 2q (for q in [2^49, 2^50)), where
-//    products of a value and a balanced twiddle (|w| <= q/2) stay below
-//    q^2 < 2^100. MI355X runs FP64 FMA at the full vector rate, which makes
-//    this about three times faster than 64-bit integer products.
+//    transform keeps every value within 8q < 2^53 (see ArF), where products of a
+//    value and a balanced twiddle (|w| <= q/2) stay below 2^102. MI355X runs FP64
+//    FMA at the full vector rate: such a product takes 6 instructions, one of a P
+//    prime by a constant 13 and of two variables 17.
 //  * ArI, for the P primes: uint64 residues, lazily reduced up to 2^64. The P
 //    primes are the largest p = 2^60 - delta = 1 (mod 2N), and delta < 2^29 for
 //    every N and count the library takes (the host checks it), so a value folds
@@ -93,8 +93,9 @@ __device__ __forceinline__ uint64_t mul_shoup(uint64_t a, uint64_t w, uint64_t w
 }
 
 // The same with the quotient's low partial product and carries left out (nq =
-// 2^64 - q): the quotient is at most 3 below Shoup's, which is at most 1 below
-// the true one, so the result is a*w mod q plus a multiple of q, in [0, 4q).
+// 2^64 - q): three fractions below 1 are dropped (of a1 s0, a0 s1 and a0 s0), whose sum
+// is below 3, so the quotient is at most 2 below Shoup's, which is at most 1 below the true
+// one, and the result is a*w mod q plus a multiple of q, in [0, 4q).
 // 13 multiplies and additions against 18.
 __device__ __forceinline__ uint64_t mul_shoup_lazy(uint64_t a, uint64_t w, uint64_t ws, uint64_t nq) {
   const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32);
@@ -220,7 +221,7 @@ __device__ __forceinline__ Tw load_tw(const uint64_t* table, uint32_t idx) {
 // With conditional subtractions in every stage and the exact Shoup quotient a
 // butterfly was 27 instructions against 19, and a key product by Montgomery's
 // reduction 39 against 17 (p_mul): (4, 2^16, 32), batch 8, 946 us then and 863
-// now; (2, 2^13, 6), one ciphertext, 30.6 and 27.1.
+// with this; (2, 2^13, 6), one ciphertext, 30.6 and 27.1.
 struct ArI {
   using T = uint64_t;
   uint64_t q, nq;

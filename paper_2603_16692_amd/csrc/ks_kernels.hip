@@ -81,9 +81,9 @@ __device__ __forceinline__ void inv_opaque(const Ar& A, typename Ar::T* v, typen
 // A word of an intermediate of the KeySwitch that one workgroup reads, once: a
 // non-temporal load, first to leave the L2, so that what is read again (the key for
 // the items of a tile, tables) and what the kernel before wrote for the next one stays.
-// (4, 2^16, 32), one ciphertext, 149 -> 141 us, batch 8, 785 -> 774; (2, 2^15, 10),
-// batch 32, 422 -> 408. Not for the key: level 13 of (4, 2^16, 32), batch 3, 151 -> 158;
-// nor for d and the transforms in place: (2, 2^15, 10), batch 32, 418.
+// (4, 2^16, 32), one ciphertext, 154 -> 142 us, batch 8, 783 -> 770; (2, 2^15, 10),
+// batch 32, 424 -> 411. Not for the key: level 13 of (4, 2^16, 32), batch 3, 151 -> 158;
+// nor for d and the transforms in place, 2% of (2, 2^15, 10), batch 32.
 __device__ __forceinline__ uint64_t ld_once(const uint64_t* p) { return __builtin_nontemporal_load(p); }
 
 // Column kernels with ONCE false are for a launch over a chunk of the targets, which
@@ -505,8 +505,9 @@ constexpr int mx_cols(int logr, int nm) { return (nm << logr) <= (logr == 5 ? 64
 // wave's own part of the LDS: one or two loads a lane, in flight with the constants
 // and stored when the rows are done. Read where each stage uses them, from two
 // addresses a wave, they took the registers that the rows need and a latency a
-// stage (ModUp of (4, 2^16, 32), batch 8, 181 -> 168 us, with the registers no longer
-// spilling); with 8 rows (7 twiddles) the detour costs 2% of (2, 2^15, 10), batch 32.
+// stage (ModUp of (4, 2^16, 32), batch 8, 181 -> 168 us; 4 of its registers still spill, 10
+// with 3 steps and 12 with 4); with 8 rows (7 twiddles) the detour costs 2% of
+// (2, 2^15, 10), batch 32.
 constexpr bool mx_twl(int logr) { return logr >= 4; }
 constexpr int mx_nt(int logr) { return mx_twl(logr) ? (4 << logr) / 64 : 1; }
 // LDS: the packed digits, and that part for each wave (16 bytes each, for P targets).
@@ -1799,9 +1800,9 @@ hipError_t by_logr(int log_r, A... a) {
 // Elements per thread of the plain block passes: 8 up to blocks of 2^12 (twice the
 // threads per block that 16 give, which small transforms need to fill the chip: -22%
 // on (2, 2^13, 6) with one ciphertext; at 2^12, -2% on modup + keymult + moddown and
-// on HMUL of (4, 2^16, 32)) and 16 beyond. The plain inverse pass and the passes of
-// KS_PLAN_HOIST_FWD take 16 at 2^12 too: one LDS exchange less, 2% of
-// (2, 2^15, 10), batch 32.
+// on HMUL of (4, 2^16, 32)) and 16 beyond. `lean`, the passes that read and write little
+// beside their block (the plain inverse ones, k_keymult_pre and k_moddown_pre), take 16 at
+// 2^12 too: one LDS exchange less, 2% of (2, 2^15, 10), batch 32.
 constexpr int loge_for(int logm, bool lean) {
   return logm >= (lean ? 12 : 13) ? 4 : (logm >= 6 ? 3 : (logm >= 4 ? 2 : 1));
 }
