@@ -40,8 +40,8 @@ OP_METRIC = {"keyswitch": "KeySwitch/s", "hmul": "HMUL/s", "hrot": "HROT/s"}
 # The rocprofv3 summaries it comes from are under profiles/.
 TRAFFIC = {"workload": "d4-n16-l32", "op": "keyswitch", "batch": 8, "plan": "Plan(DPOB, chunks=1, log_r=4, mfma)",
            "kernel": "moddown_blocks",
-           "fetch_kib": 467213.6, "fetch_scale": 2.0, "write_kib": 262150.9, "write_scale": 1.0,
-           "sources_sha256": "bed8a09ca0335adc75b4e4c4ef0fb09d92c0c2bccaf2975fe750c38d5b383c46"}
+           "fetch_kib": 467215.2, "fetch_scale": 2.0, "write_kib": 262151.2, "write_scale": 1.0,
+           "sources_sha256": "0319ae93d29cd8d8565924cf0a6f0f7820e7efe74848d57342479fbcc9146feb"}
 TRAFFIC_SOURCES = ["paper_2603_16692_amd/csrc/ks_kernels.hip", "paper_2603_16692_amd/csrc/ks_device.hpp"]
 
 
